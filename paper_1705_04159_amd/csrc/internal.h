@@ -121,13 +121,20 @@ struct bpmf_ctx {
     int hyp_blocks = 0;
     double *hyp_stats[2] = {};    // [K + K(K+1)/2]
     double *hyp_scratch[2] = {};  // [4 * K * K + 8 * K]
-    int *hyp_status = nullptr;    // device flags, 1 = ok: [0] hyper draw, [1] row draws (pivots)
+    // flags, 1 = ok: [0] hyper draw, [1] row draws (pivots); pinned coherent host
+    // memory that kernels clear in place, so that reading them after a
+    // call's one synchronisation costs no copy
+    int *hyp_status = nullptr;
     int hyp_lds_max = 65536;      // LDS bytes the draw kernel may use
     // split partials
     void *part = nullptr;
     int64_t part_slots = 0;
     // device counters: [0] = t, [1] = t0 of the running graph, [2] = running-mean count
     uint32_t *ctr = nullptr;
+    // staging of host factor copies: two chunks each on the device and in pinned
+    // host memory
+    void *io_dev = nullptr, *io_pin = nullptr;
+    hipEvent_t io_ev[2] = {};
     // predict scratch for user-supplied pairs
     int32_t *q_row = nullptr, *q_col = nullptr;
     float *q_out = nullptr;
@@ -175,6 +182,11 @@ hipError_t launch_predict_pairs(bpmf_ctx *c, int64_t n, const int32_t *row, cons
 // Caller ids to internal rows in place (relabelled contexts): row[e] and col[e]
 // through d_int_of of the user and movie sides.
 hipError_t launch_map_pairs(bpmf_ctx *c, int64_t n, int32_t *row, int32_t *col, hipStream_t s);
+// Rows [r0, r0 + n) of a factor in the caller's order, without the padding,
+// into `packed` (pack) or from it: rows of Kw 4-byte words, the factor's ldw
+// words apart; row r is X's row map[r] (map null: row r).
+hipError_t launch_pack_rows(bool pack, uint32_t *X, int Kw, int ldw, const int32_t *map, int64_t r0,
+                            int64_t n, uint32_t *packed, hipStream_t s);
 // Device address of the staging area of bpmf_predict_noalloc on c's device.
 hipError_t predict_scratch_init(bpmf_ctx *c);
 // Factor initialisation from Philox normals.

@@ -319,6 +319,39 @@ hipError_t launch_map_pairs(bpmf_ctx *c, int64_t n, int32_t *row, int32_t *col, 
     return hipGetLastError();
 }
 
+// Rows of a factor to or from a packed chunk, one thread per 4-byte word.
+// Bound by the PCIe copy that follows (55 GB/s against TB/s here), so words
+// rather than float4: K of any remainder takes the same path.
+template <bool PACK>
+__global__ __launch_bounds__(256) void pack_rows(uint32_t *__restrict__ X, int Kw, int ldw,
+                                                 const int32_t *__restrict__ map, int64_t r0, uint32_t words,
+                                                 uint32_t *__restrict__ packed)
+{
+    const uint32_t e = blockIdx.x * 256u + threadIdx.x;
+    if (e >= words) return;
+    const uint32_t q = e / (uint32_t)Kw;
+    const int64_t r = r0 + q;
+    uint32_t *x = X + (size_t)(map ? (int64_t)map[r] : r) * ldw + (e - q * (uint32_t)Kw);
+    if (PACK)
+        packed[e] = *x;
+    else
+        *x = packed[e];
+}
+
+hipError_t launch_pack_rows(bool pack, uint32_t *X, int Kw, int ldw, const int32_t *map, int64_t r0,
+                            int64_t n, uint32_t *packed, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    const uint32_t words = (uint32_t)(n * Kw);  // a chunk: below 2^32
+    if (pack)
+        hipLaunchKernelGGL((pack_rows<true>), dim3((words + 255) / 256), dim3(256), 0, s, X, Kw, ldw, map, r0,
+                           words, packed);
+    else
+        hipLaunchKernelGGL((pack_rows<false>), dim3((words + 255) / 256), dim3(256), 0, s, X, Kw, ldw, map, r0,
+                           words, packed);
+    return hipGetLastError();
+}
+
 // The device address of this GPU's staging area, looked up once per device
 // with that device current (called by bpmf_create).
 hipError_t predict_scratch_init(bpmf_ctx *c)
