@@ -12,32 +12,32 @@
 // A_kk = sqrt(chi2(nu* - k)), k = 0..K-1, and N(0,1) below the diagonal in
 // row-major order), then mu = mu* + chol(beta* Lambda)^-T z.
 //
-// Three launches: per-block FP64 moment sums over row chunks (S is formed as
-// sum x x^T - n xbar xbar^T; on the FP64 matrix cores for K <= 112), a
-// fixed-order reduction of the block sums (coalesced over entries), and one
-// workgroup for the K x K algebra.  The
-// algebra avoids forming W* and two of the three factorisations:
+// Three launches: per-block FP64 moment sums over row chunks on the FP64 matrix
+// cores (S is formed as sum x x^T - n xbar xbar^T); a fixed-order reduction of
+// the block sums, whose spare workgroups draw the noise of the step (it
+// depends on the counters alone); and one workgroup for the K x K algebra.
+// The algebra avoids forming W* and two of the three factorisations:
 //   * L_W is obtained from one Cholesky of the index-reversed W*^-1:
 //     J W*^-1 J = C C^T gives W*^-1 = (J C J)(J C J)^T with J C J upper
 //     triangular, hence W* = (J C J)^-T (J C J)^-1 and, by uniqueness of the
-//     Cholesky factor, L_W = J C^-T J, i.e. L_W[i][j] = (C^-1)[K-1-j][K-1-i];
+//     Cholesky factor, L_W = J C^-T J, i.e. L_W[i][j] = (C^-1)[n-1-j][n-1-i];
 //   * B = L_W A is lower triangular with a positive diagonal, so it is the
 //     Cholesky factor of Lambda, and chol(beta* Lambda) = sqrt(beta*) B:
 //     mu = mu* + B^-T z / sqrt(beta*).
-// All K x K matrices are packed lower triangles in LDS when they fit.
+// The order is padded to n = 16 ceil(K / 16) with the identity, which every
+// step carries through (reversed, the padding leads), so that all matrices are
+// whole 16 x 16 blocks in LDS and every product runs on the matrix cores.
 #include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
 #include "rng_device.h"
+#include "row_common.h"
 
 namespace bpmf {
 namespace {
 
-constexpr int kThreads = 256;      // moment sums (non-matrix-core path)
-constexpr int kDrawThreads = 1024;  // the K x K algebra of the draw (one workgroup)
-
-__device__ __forceinline__ int pk(int i, int j) { return i * (i + 1) / 2 + j; }
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void tri_index(int e, int &i, int &j)
 {
@@ -51,76 +51,65 @@ __device__ __forceinline__ void tri_index(int e, int &i, int &j)
 __device__ __forceinline__ double as_f64(float v) { return (double)v; }
 __device__ __forceinline__ double as_f64(double v) { return v; }
 
-// Block b sums rows [b*chunk, min(rows, (b+1)*chunk)).  Entry e < K is
-// sum x_e (taken as x_e * 1 with a constant 1 appended to each staged row),
-// entry K + pk(i,j) is sum x_i x_j.  NE = entries per thread.
-template <int NE, typename XT>
-__global__ __launch_bounds__(kThreads) void hyper_moments(int K, const XT *__restrict__ X, int ld,
-                                                          int64_t rows, int64_t chunk,
-                                                          int tile_rows, double *__restrict__ part)
-{
-    extern __shared__ __align__(16) char smem_raw[];
-    double *tileX = (double *)smem_raw;  // tile_rows * (K + 1)
-    const int tid = threadIdx.x;
-    const int KA = K + 1;
-    const int E = K + K * (K + 1) / 2;
-    const int64_t r0 = (int64_t)blockIdx.x * chunk;
-    const int64_t r1 = min<int64_t>(rows, r0 + chunk);
-    double acc[NE];
-    int ia[NE], ja[NE];
-#pragma unroll
-    for (int m = 0; m < NE; ++m) {
-        acc[m] = 0.0;
-        int e = tid + m * kThreads, i = 0, j = K;
-        if (e < K) {
-            i = e;
-        } else if (e < E) {
-            tri_index(e - K, i, j);
-        }
-        ia[m] = i;
-        ja[m] = j;
-    }
-    for (int64_t base = r0; base < r1; base += tile_rows) {
-        const int cnt = (int)min<int64_t>(tile_rows, r1 - base);
-        for (int q = tid; q < cnt * KA; q += kThreads) {
-            const int rr = q / KA, k = q - rr * KA;
-            tileX[q] = k < K ? as_f64(X[(size_t)(base + rr) * ld + k]) : 1.0;
-        }
-        __syncthreads();
-        for (int rr = 0; rr < cnt; ++rr) {
-            const double *x = tileX + rr * KA;
-#pragma unroll
-            for (int m = 0; m < NE; ++m) acc[m] += x[ia[m]] * x[ja[m]];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int m = 0; m < NE; ++m) {
-        const int e = tid + m * kThreads;
-        if (e < E) part[(size_t)blockIdx.x * E + e] = acc[m];
-    }
-}
+// The block sums on the FP64 matrix cores: four wavefronts per block of rows,
+// four rows per v_mfma_f64_16x16x4f64 step -- lane l holds component
+// 16*bi + (l % 16) of row 4g + l / 16 as an FP64 value (FP32 factors convert
+// exactly), which is both the A operand of block row bi and the B operand of
+// block column bj, so only the nb(nb+1)/2 lower 16x16 blocks of X^T X are
+// accumulated; sum x on the VALU from the same registers.  (The FP64
+// instruction returns D[4 v + l / 16][l % 16] in value v of lane l, unlike the
+// FP32 one.)  Products of FP32 values are exact in FP64, and every sum is in
+// FP64 in a fixed order.  The rows of the next four steps are in flight during
+// a step's products.  Up to K = 64 each wave takes a quarter of the rows and
+// the four sums are added in LDS; above, where one wave's accumulators would
+// fill the register file, each wave takes a quarter of the 16x16 blocks of
+// every row (the rows come from the L1 three times in four).  Either way a
+// block's sums leave the GPU's registers once for four waves: writing and
+// reading them back (41 KB at K = 100) costs more than the rows themselves
+// (120,047 rows, K = 100, 1024 one-wave blocks: 46 us, and 14 us more in the
+// reduction).
+constexpr int kMomentsAhead = 4;
+constexpr int kMomentsWaves = 4;
 
-// The same block sums on the FP64 matrix cores (nb = ceil(K/16) <= 7): one
-// wavefront per block of rows, four rows per v_mfma_f64_16x16x4f64 step --
-// lane l holds component 16*bi + (l % 16) of row 4g + l / 16 as an FP64
-// value (FP32 factors convert exactly), which is both the A operand of block
-// row bi and the B operand of block column bj, so only the nb(nb+1)/2 lower
-// 16x16 blocks of X^T X are accumulated; sum x on the VALU from the same
-// registers.  (The FP64 instruction returns D[4 v + l / 16][l % 16] in value v
-// of lane l, unlike the FP32 one.)  Products of FP32 values are exact in
-// FP64, and every sum is in FP64 in a fixed order.
-typedef double doublex4 __attribute__((ext_vector_type(4)));
+// Rows of one wave's range of the factor, read through its range check: rows
+// past the range are 0, components >= K whatever follows (their sums are
+// ignored).
+template <int NB, typename XT>
+struct MomentRows {
+    __amdgpu_buffer_rsrc_t src;
+    uint32_t off, step;  // of this lane's row of the next step, bytes of four rows
+    __device__ __forceinline__ MomentRows(const XT *X, int ld, int64_t r0, int64_t r1)
+    {
+        const int lane = threadIdx.x & 63;
+        src = make_rsrc(X + (size_t)r0 * ld, (uint32_t)((r1 - r0) * ld * sizeof(XT)));
+        off = (uint32_t)(((lane >> 4) * ld + (lane & 15)) * sizeof(XT));
+        step = (uint32_t)(4 * ld * sizeof(XT));
+    }
+    __device__ __forceinline__ void load(XT (&y)[NB])
+    {
+#pragma unroll
+        for (int bi = 0; bi < NB; ++bi) {
+            if constexpr (sizeof(XT) == 4)
+                y[bi] = buf_f32(src, off + 64u * bi);
+            else
+                y[bi] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(src, (int)(off + 128u * bi), 0, 0));
+        }
+        off += step;
+    }
+};
 
 template <int NB, typename XT>
-__global__ __launch_bounds__(64) void hyper_moments_mfma(int K, const XT *__restrict__ X, int ld,
-                                                         int64_t rows, int64_t chunk,
-                                                         double *__restrict__ part)
+__global__ __launch_bounds__(64 * kMomentsWaves) void hyper_moments_mfma(int K, const XT *__restrict__ X, int ld,
+                                                                         int64_t rows, int64_t chunk,
+                                                                         double *__restrict__ part)
 {
     constexpr int NBLK = NB * (NB + 1) / 2;
-    const int lane = threadIdx.x;
+    constexpr int A = kMomentsAhead;
+    __shared__ double sums[NBLK * 256 + 16 * NB];  // value v of lane l of block q at 256 q + 64 v + l, then sum x
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, kq = lane >> 4;
-    const int64_t r0 = (int64_t)blockIdx.x * chunk;
+    const int64_t r0 = min<int64_t>(rows, ((int64_t)blockIdx.x * kMomentsWaves + wave) * chunk);
     const int64_t r1 = min<int64_t>(rows, r0 + chunk);
     const int E = K + K * (K + 1) / 2;
     doublex4 acc[NBLK];
@@ -129,422 +118,644 @@ __global__ __launch_bounds__(64) void hyper_moments_mfma(int K, const XT *__rest
     double sx[NB];
 #pragma unroll
     for (int bi = 0; bi < NB; ++bi) sx[bi] = 0.0;
-    // rows of the next step are loaded while this step's products run
-    auto load = [&](int64_t base, XT (&y)[NB]) {
-        const int64_t r = base + kq;
+    MomentRows<NB, XT> in(X, ld, r0, r1);
+    XT ring[A][NB];
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi) {
-            const int c = 16 * bi + col;
-            y[bi] = (r < r1 && c < K) ? X[(size_t)r * ld + c] : XT(0);
-        }
-    };
-    XT ycur[NB], ynext[NB];
-    load(r0, ycur);
-    for (int64_t base = r0; base < r1; base += 4) {
-        load(base + 4, ynext);
-        double y[NB];
+    for (int a = 0; a < A; ++a) in.load(ring[a]);
+    for (int64_t base = r0; base < r1; base += 4 * A) {
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi) {
-            y[bi] = as_f64(ycur[bi]);
-            sx[bi] += y[bi];
-        }
-        int q = 0;
+        for (int a = 0; a < A; ++a) {  // steps past r1 multiply zeros
+            double y[NB];
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj <= bi; ++bj) {
-                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[bi], y[bj], acc[q], 0, 0, 0);
-                ++q;
+            for (int bi = 0; bi < NB; ++bi) {
+                y[bi] = as_f64(ring[a][bi]);
+                sx[bi] += y[bi];
             }
+            in.load(ring[a]);
+            int q = 0;
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi) ycur[bi] = ynext[bi];
+            for (int bi = 0; bi < NB; ++bi)
+#pragma unroll
+                for (int bj = 0; bj <= bi; ++bj) {
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[bi], y[bj], acc[q], 0, 0, 0);
+                    ++q;
+                }
+        }
     }
-    double *dst = part + (size_t)blockIdx.x * E;
 #pragma unroll
     for (int bi = 0; bi < NB; ++bi) {
-        double t = sx[bi];
+        sx[bi] += __shfl_xor(sx[bi], 16);
+        sx[bi] += __shfl_xor(sx[bi], 32);
+    }
+    for (int w = 0; w < kMomentsWaves; ++w) {  // in wave order
+        if (w == wave) {
+#pragma unroll
+            for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    double *d = sums + 256 * q + 64 * v + lane;
+                    *d = w == 0 ? acc[q][v] : *d + acc[q][v];
+                }
+            if (kq == 0)
+#pragma unroll
+                for (int bi = 0; bi < NB; ++bi) {
+                    double *d = sums + NBLK * 256 + 16 * bi + col;
+                    *d = w == 0 ? sx[bi] : *d + sx[bi];
+                }
+        }
+        __syncthreads();
+    }
+    double *dst = part + (size_t)blockIdx.x * E;
+    for (int k = threadIdx.x; k < K; k += 64 * kMomentsWaves) dst[k] = sums[NBLK * 256 + k];
+#pragma unroll
+    for (int bi = 0; bi < NB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj <= bi; ++bj) {
+            // FP64 result layout: lane l, value v holds D[4 v + l / 16][l % 16]
+            const int i = 16 * bi + 4 * wave + kq, j = 16 * bj + col;
+            if (i < K && j <= i) dst[K + pk(i, j)] = sums[256 * pk(bi, bj) + 64 * wave + lane];
+        }
+}
+
+// Wave W's blocks q = W, W + 4, ... of rows [r0, r1), and sum x of its
+// components' blocks.
+template <int NB, int W, typename XT>
+__device__ __forceinline__ void moments_quarter(int K, const XT *__restrict__ X, int ld, int64_t r0, int64_t r1,
+                                                double *__restrict__ dst)
+{
+    constexpr int NBLK = NB * (NB + 1) / 2;
+    constexpr int MINE = (NBLK - W + kMomentsWaves - 1) / kMomentsWaves;
+    constexpr int A = kMomentsAhead;
+    const int lane = threadIdx.x & 63;
+    const int col = lane & 15, kq = lane >> 4;
+    doublex4 acc[MINE];
+#pragma unroll
+    for (int m = 0; m < MINE; ++m) acc[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double sx[(NB + kMomentsWaves - 1) / kMomentsWaves] = {};
+    XT ring[A][NB];
+    MomentRows<NB, XT> in(X, ld, r0, r1);
+#pragma unroll
+    for (int a = 0; a < A; ++a) in.load(ring[a]);
+    for (int64_t base = r0; base < r1; base += 4 * A) {
+#pragma unroll
+        for (int a = 0; a < A; ++a) {  // steps past r1 multiply zeros
+            double y[NB];
+#pragma unroll
+            for (int bi = 0; bi < NB; ++bi) y[bi] = as_f64(ring[a][bi]);
+#pragma unroll
+            for (int bi = W; bi < NB; bi += kMomentsWaves) sx[bi / kMomentsWaves] += y[bi];
+            in.load(ring[a]);
+            static_for<0, NB>([&](auto ic) {
+                static_for<0, decltype(ic)::value + 1>([&](auto jc) {
+                    constexpr int i = decltype(ic)::value, j = decltype(jc)::value, q = i * (i + 1) / 2 + j;
+                    if constexpr (q % kMomentsWaves == W)
+                        acc[q / kMomentsWaves] =
+                            __builtin_amdgcn_mfma_f64_16x16x4f64(y[i], y[j], acc[q / kMomentsWaves], 0, 0, 0);
+                });
+            });
+        }
+    }
+#pragma unroll
+    for (int bi = W; bi < NB; bi += kMomentsWaves) {
+        double t = sx[bi / kMomentsWaves];
         t += __shfl_xor(t, 16);
         t += __shfl_xor(t, 32);
         const int c = 16 * bi + col;
         if (kq == 0 && c < K) dst[c] = t;
     }
-    int q = 0;
+    static_for<0, NB>([&](auto ic) {
+        static_for<0, decltype(ic)::value + 1>([&](auto jc) {
+            constexpr int bi = decltype(ic)::value, bj = decltype(jc)::value, q = bi * (bi + 1) / 2 + bj;
+            if constexpr (q % kMomentsWaves == W)
 #pragma unroll
-    for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj <= bi; ++bj) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                // FP64 result layout: lane l, value v holds D[4 v + l / 16][l % 16]
-                const int i = 16 * bi + 4 * v + kq, j = 16 * bj + col;
-                if (i < K && j <= i) dst[K + pk(i, j)] = acc[q][v];
-            }
-            ++q;
-        }
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * bi + 4 * v + kq, j = 16 * bj + col;
+                    if (i < K && j <= i) dst[K + pk(i, j)] = acc[q / kMomentsWaves][v];
+                }
+        });
+    });
 }
 
-// stats[e] = sum over blocks of part[b][e], in a fixed order, in two passes
-// of one-wave workgroups (which fit beside the row kernels of the other
-// side): wave (w, g) of the first pass takes entries 64 w .. 64 w + 63 (lane
-// l entry 64 w + l, so every load of a wave is 512 contiguous bytes) and
-// sums blocks g, g + 16, g + 32, ...; the second pass adds the 16 sums of
-// each entry in order of g.
-constexpr int kRedGroups = 16;
-__global__ __launch_bounds__(64) void hyper_reduce_groups(int E, int nblk, const double *__restrict__ part,
-                                                         double *__restrict__ red)
+template <int NB, typename XT>
+__global__ __launch_bounds__(64 * kMomentsWaves, 2) void hyper_moments_wide(int K, const XT *__restrict__ X, int ld,
+                                                                            int64_t rows, int64_t chunk,
+                                                                            double *__restrict__ part)
 {
-    const int lane = threadIdx.x;
-    const int e = blockIdx.x * 64 + lane;
-    const int g = blockIdx.y;
-    if (e >= E) return;
+    const int64_t r0 = min<int64_t>(rows, (int64_t)blockIdx.x * chunk * kMomentsWaves);
+    const int64_t r1 = min<int64_t>(rows, r0 + chunk * kMomentsWaves);
+    double *dst = part + (size_t)blockIdx.x * (K + K * (K + 1) / 2);
+    switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: moments_quarter<NB, 0>(K, X, ld, r0, r1, dst); break;
+    case 1: moments_quarter<NB, 1>(K, X, ld, r0, r1, dst); break;
+    case 2: moments_quarter<NB, 2>(K, X, ld, r0, r1, dst); break;
+    default: moments_quarter<NB, 3>(K, X, ld, r0, r1, dst); break;
+    }
+}
+
+// stats[e] = sum over blocks of part[b][e], in a fixed order: a workgroup takes
+// 16 entries (128 contiguous bytes of each block's sums), thread (sub, e) adds
+// blocks sub, sub + 32, sub + 64, ..., then the 32 sums are added across lanes
+// and wavefronts.  The workgroups past the entries draw the step's noise:
+// noise[0, K(K-1)/2) the normals below the Bartlett factor's diagonal in
+// row-major order, the next K the mean's normals, the last K the diagonal
+// sqrt(chi2(nu* - k)).  Replaces two passes of one-wave workgroups (9.6 and
+// 3.4 us at K = 32 with 2048 blocks) and takes the transcendentals off the
+// draw's one workgroup.
+constexpr int kRedThreads = 512;
+
+__global__ __launch_bounds__(kRedThreads) void hyper_reduce(int K, int nblk, const double *__restrict__ part,
+                                                            double *__restrict__ stats, int entry_groups,
+                                                            double nu_s, uint64_t seed, uint32_t stream,
+                                                            const uint32_t *__restrict__ ctr, uint32_t t_off,
+                                                            double *__restrict__ noise, int *__restrict__ status)
+{
+    __shared__ double ws[kRedThreads / 64][16];
+    const int tid = threadIdx.x;
+    const int E = K + K * (K + 1) / 2;
+    if ((int)blockIdx.x >= entry_groups) {
+        const uint32_t t = ctr[0] + t_off;
+        const int n_low = K * (K - 1) / 2, b_low = (n_low + 3) / 4, b_mu = (K + 3) / 4;
+        const int job = ((int)blockIdx.x - entry_groups) * kRedThreads + tid;
+        if (job < b_low + b_mu) {
+            const bool low = job < b_low;
+            const int blk = low ? job : job - b_low;
+            double z[4];
+            normals_block(seed, (uint32_t)blk, t, stream, low ? 1u : 2u, 0u, z);
+            for (int l = 0; l < 4; ++l)
+                if (4 * blk + l < (low ? n_low : K)) noise[(low ? 0 : n_low) + 4 * blk + l] = z[l];
+        } else if (job - b_low - b_mu < K) {
+            const int k = job - b_low - b_mu;
+            int ok = 1;
+            noise[n_low + K + k] = sqrt(chi_square(seed, stream, t, (uint32_t)k, nu_s - (double)k, &ok));
+            if (!ok) *status = 0;
+        }
+        return;
+    }
+    const int e = (int)blockIdx.x * 16 + (tid & 15);
     double s = 0.0;
+    if (e < E) {
 #pragma unroll 8
-    for (int b = g; b < nblk; b += kRedGroups) s += part[(size_t)b * E + e];
-    red[(size_t)g * E + e] = s;
-}
-
-__global__ __launch_bounds__(64) void hyper_reduce(int E, const double *__restrict__ red,
-                                                   double *__restrict__ stats)
-{
-    const int e = blockIdx.x * 64 + threadIdx.x;
-    if (e >= E) return;
-    double t = 0.0;
+        for (int b = tid >> 4; b < nblk; b += kRedThreads / 16) s += part[(size_t)b * E + e];
+    }
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if ((tid & 63) < 16) ws[tid >> 6][tid & 15] = s;
+    __syncthreads();
+    if (tid < 16 && e < E) {
+        double r = 0.0;
 #pragma unroll
-    for (int g = 0; g < kRedGroups; ++g) t += red[(size_t)g * E + e];
-    stats[e] = t;
+        for (int w = 0; w < kRedThreads / 64; ++w) r += ws[w][tid];
+        stats[e] = r;
+    }
 }
 
-// In-place Cholesky of a packed lower K x K matrix (K <= 128) by the whole
-// workgroup, right-looking with the column scaling deferred: step k
-// subtracts P[i][k] P[j][k] / P[k][k] from the trailing entries (i >= j > k),
-// reading column k unscaled; at the end column k is divided by
-// sqrt(P[k][k]) and the pivot replaced by the root.  Steps go in pairs, one
-// barrier per pair: every thread forms column k + 1 after step k from
-// columns k and k + 1 as they were (the same operations in the same order
-// as one step after the other), applies both steps to its trailing entries
-// (j >= k + 2), and the pair's own update of column k + 1 is written in the
-// next phase, when nothing reads that column.  Clears *ok on a
-// non-positive pivot (which is then taken as 1).
-template <int NT>
-__device__ void chol_packed(int K, double *P, int *ok)
+// ---- block algebra in LDS ----
+// A matrix of nb x nb lower 16 x 16 blocks: block (i, j), i >= j, is row-major
+// at bo(i, j) with rows 17 doubles apart (so that the 16 lanes of an operand
+// read, one row each, fall into different banks).  Lane (g, c) = (l / 16, l %
+// 16) of a wave feeds X[c][4 s + g] (A operand) and Y[4 s + g][c] (B operand)
+// in step s of a block product and receives D[4 v + g][c] in value v.
+constexpr int kBS = 17;
+constexpr int kBlk = 16 * kBS;
+
+__device__ __forceinline__ int bo(int i, int j) { return pk(i, j) * kBlk; }
+__device__ __forceinline__ int el(int i, int j) { return bo(i >> 4, j >> 4) + (i & 15) * kBS + (j & 15); }
+
+__device__ __forceinline__ void lds_wave_sync()
 {
-    __shared__ double root[128];
-    const int tid = threadIdx.x;
-    const int ti = tid & 31, tj = tid >> 5;  // a 32 x (NT / 32) tiling of the trailing triangle
-    auto inv_pivot = [&](int k) {
-        const double d = P[pk(k, k)];
-        return 1.0 / (d > 0.0 ? d : 1.0);
-    };
-    // column c's update by step c - 1 (the second column of the pair before)
-    auto pending = [&](int c) {
-        const double rd = inv_pivot(c - 1), p = P[pk(c, c - 1)];
-        for (int i = c + tid; i < K; i += NT) P[pk(i, c)] -= (P[pk(i, c - 1)] * rd) * p;
-    };
-    int k = 0;
-    for (; k + 2 <= K - 1; k += 2) {
-        if (k >= 2) pending(k - 1);
-        const double rd0 = inv_pivot(k);
-        const double p10 = P[pk(k + 1, k)];
-        double d1 = P[pk(k + 1, k + 1)] - (p10 * rd0) * p10;
-        const double rd1 = 1.0 / (d1 > 0.0 ? d1 : 1.0);
-        for (int i = k + 2 + ti; i < K; i += 32) {
-            const double pi0 = P[pk(i, k)] * rd0;
-            const double pi1 = (P[pk(i, k + 1)] - pi0 * p10) * rd1;
-            for (int j = k + 2 + tj; j <= i; j += NT / 32) {
-                const double aj = P[pk(j, k)];
-                const double qj = P[pk(j, k + 1)] - (aj * rd0) * p10;
-                double v = P[pk(i, j)];
-                v -= pi0 * aj;
-                v -= pi1 * qj;
-                P[pk(i, j)] = v;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// acc += sgn X Y^T (both blocks row-major): the A operand of each.
+__device__ __forceinline__ doublex4 mul_abt(const double *X, const double *Y, double sgn, doublex4 acc, int g, int c)
+{
+    double a[4], b[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        a[s] = X[c * kBS + 4 * s + g];
+        b[s] = Y[c * kBS + 4 * s + g];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sgn * a[s], b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+// acc += X Y.
+__device__ __forceinline__ doublex4 mul_ab(const double *X, const double *Y, doublex4 acc, int g, int c)
+{
+    double a[4], b[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        a[s] = X[c * kBS + 4 * s + g];
+        b[s] = Y[(4 * s + g) * kBS + c];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+__device__ __forceinline__ doublex4 load_blk(const double *X, int g, int c)
+{
+    doublex4 r;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[v] = X[(4 * v + g) * kBS + c];
+    return r;
+}
+
+__device__ __forceinline__ void store_blk(double *X, doublex4 r, int g, int c)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[(4 * v + g) * kBS + c] = r[v];
+}
+
+// x of lane k of each 16-lane row, and x of 16-lane row R, for every lane.
+template <int k>
+__device__ __forceinline__ double lane_of_row(double x)
+{
+    const uint64_t w = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, 0x150 + k, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(w >> 32), 0x150 + k, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+template <int R>
+__device__ __forceinline__ uint32_t row_of_wave(uint32_t x)
+{
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const uint32_t y = (R & 1) ? p[1] : p[0];
+    const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return (R & 2) ? q[1] : q[0];
+}
+
+template <int R>
+__device__ __forceinline__ double row_of_wave(double x)
+{
+    const uint64_t w = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = row_of_wave<R>((uint32_t)w), hi = row_of_wave<R>((uint32_t)(w >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// 1 / d to an ulp or so for normal d (estimate and two Newton steps: half the
+// dependent instructions of a division).
+__device__ __forceinline__ double rcp_f64(double d)
+{
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
+
+// One wave: the whole symmetric block D = L L^T replaced by X = L^-1.  Lane
+// (g, c) holds rows 4 v + g of column c; column c > k takes -(d_kc / d_kk)
+// times column k on the stacked [G; d] (row k leaves d for G = L_unit^-T once
+// it has served as pivot row), the pivot row coming from the lane row that
+// holds it.  X = D^-1/2 G^T.  Clears *ok on a non-positive pivot (taken as 1).
+__device__ __forceinline__ void factor_block(double *D, int g, int c, int *ok)
+{
+    double u[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) u[v] = D[(4 * v + g) * kBS + c];
+    double mydiag = 1.0;
+    static_for<0, 16>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        constexpr int gk = k & 3, vk = k >> 2;
+        const double pr = row_of_wave<gk>(u[vk]);  // row k of column c
+        const double d = lane_of_row<k>(pr);
+        const double dk = d > 0.0 ? d : 1.0;
+        if (c == k) mydiag = d;
+        const double nf = c > k ? -pr * rcp_f64(dk) : 0.0;
+        if (g == gk) u[vk] = c == k ? 1.0 : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) u[v] = fma(nf, lane_of_row<k>(u[v]), u[v]);
+    });
+    if (!(mydiag > 0.0)) *ok = 0;
+    const double inv_s = 1.0 / sqrt(mydiag > 0.0 ? mydiag : 1.0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) D[c * kBS + 4 * v + g] = u[v] * inv_s;
+}
+
+// Workgroup: in-place blocked Cholesky of the lower blocks T (diagonal blocks
+// whole); the diagonal blocks end as the inverses of the factor's.  The first
+// wave updates and factors the next diagonal block while the others update
+// the remaining trailing blocks: two barriers per block column.  (K = 64: 36 us
+// and 32 barriers when it went by pairs of columns.)
+template <int NW>
+__device__ void chol_blocks(int nb, double *T, int *ok)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, c = lane & 15;
+    for (int kb = 0; kb < nb; ++kb) {
+        auto trail = [&](int i, int j) {
+            double *D = T + bo(i, j);
+            store_blk(D, mul_abt(T + bo(i, kb - 1), T + bo(j, kb - 1), -1.0, load_blk(D, g, c), g, c), g, c);
+        };
+        if (wave == 0) {
+            if (kb > 0) {
+                trail(kb, kb);
+                lds_wave_sync();
+            }
+            factor_block(T + bo(kb, kb), g, c, ok);
+        } else if (kb > 0) {
+            const int m = nb - kb;
+            for (int q = wave; q < m * (m + 1) / 2; q += NW - 1) {
+                int i, j;
+                tri_index(q, i, j);
+                trail(kb + i, kb + j);
             }
         }
         __syncthreads();
-    }
-    if (k >= 2) pending(k - 1);
-    if (k == K - 2) {  // one step left: column K - 2 onto the last pivot
-        if (tid == 0) {
-            const double pik = P[pk(K - 1, k)] * inv_pivot(k);
-            P[pk(K - 1, K - 1)] -= pik * P[pk(K - 1, k)];
-        }
-    }
-    __syncthreads();
-    for (int kk = tid; kk < K; kk += NT) {
-        const double d = P[pk(kk, kk)];
-        if (!(d > 0.0)) *ok = 0;
-        root[kk] = sqrt(d > 0.0 ? d : 1.0);
-    }
-    __syncthreads();
-    const int KK2 = K * (K + 1) / 2;
-    for (int e = tid; e < KK2; e += NT) {
-        int i, j;
-        tri_index(e, i, j);
-        P[e] = i == j ? root[j] : P[e] / root[j];
-    }
-    __syncthreads();
-}
-
-// X = C^-1 for a packed lower C (X packed lower, distinct storage): forward
-// substitution on the identity with the row scaling deferred: step k
-// subtracts C[i][k] X[k][j] / C[k][k] from the rows i > k, X[k] still
-// unscaled; every row i is divided by C[i][i] at the end.  Steps go in
-// pairs, one barrier per pair, as in chol_packed: row k + 1 after step k is
-// formed by every thread that needs it and written in the next phase.
-template <int NT>
-__device__ void tri_inverse_packed(int K, const double *C, double *Xp)
-{
-    const int tid = threadIdx.x;
-    const int KK2 = K * (K + 1) / 2;
-    for (int e = tid; e < KK2; e += NT) {
-        int i, j;
-        tri_index(e, i, j);
-        Xp[e] = i == j ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    const int ti = tid & 31, tj = tid >> 5;  // a 32 x (NT / 32) tiling of rows i > k, columns j <= k
-    // row r's update by step r - 1 (the second row of the pair before)
-    auto pending = [&](int r) {
-        const double c = C[pk(r, r - 1)] * (1.0 / C[pk(r - 1, r - 1)]);  // as in the pair
-        for (int j = tid; j <= r - 1; j += NT) Xp[pk(r, j)] -= c * Xp[pk(r - 1, j)];
-    };
-    int k = 0;
-    for (; k + 2 <= K - 1; k += 2) {
-        if (k >= 2) pending(k - 1);
-        const double rck0 = 1.0 / C[pk(k, k)], rck1 = 1.0 / C[pk(k + 1, k + 1)];
-        const double c10 = C[pk(k + 1, k)] * rck0;
-        for (int i = k + 2 + ti; i < K; i += 32) {
-            const double ci0 = C[pk(i, k)] * rck0, ci1 = C[pk(i, k + 1)] * rck1;
-            for (int j = tj; j <= k + 1; j += NT / 32) {
-                const double xk = j <= k ? Xp[pk(k, j)] : 0.0;
-                const double xk1 = j <= k ? Xp[pk(k + 1, j)] - c10 * xk : Xp[pk(k + 1, j)];
-                double v = Xp[pk(i, j)];
-                if (j <= k) v -= ci0 * xk;
-                v -= ci1 * xk1;
-                Xp[pk(i, j)] = v;
-            }
+        for (int i = kb + 1 + wave; i < nb; i += NW) {
+            double *D = T + bo(i, kb);
+            store_blk(D, mul_abt(D, T + bo(kb, kb), 1.0, doublex4{0.0, 0.0, 0.0, 0.0}, g, c), g, c);
         }
         __syncthreads();
     }
-    if (k >= 2) pending(k - 1);
-    if (k == K - 2) {  // one step left: row K - 1 from row K - 2
-        const double c = C[pk(K - 1, k)] * (1.0 / C[pk(k, k)]);
-        for (int j = tid; j <= k; j += NT) Xp[pk(K - 1, j)] -= c * Xp[pk(k, j)];
-    }
-    __syncthreads();
-    for (int e = tid; e < KK2; e += NT) {
-        int i, j;
-        tri_index(e, i, j);
-        Xp[e] /= C[pk(i, i)];
-    }
-    __syncthreads();
 }
 
-// The lower 16 x 16 blocks of a K x K product D = X Y on the FP64 matrix
-// cores (v_mfma_f64_16x16x4_f64), the workgroup's waves taking the blocks
-// in turn: block (bi, bj), bi >= bj, sums k over [k0, k1) = krange(bi, bj)
-// in steps of four, lane l feeding X[16 bi + l % 16][k + l / 16] as the A
-// operand and Y[k + l / 16][16 bj + l % 16] as the B operand (xf and yf
-// return 0 outside their matrices' triangles and past K); out(i, j, d)
-// receives every D[i][j] with j <= i < K (value v of lane l is
-// D[4 v + l / 16][l % 16] of the block).  Every wave runs uniform loops.
-template <int NT, typename XF, typename YF, typename KR, typename OUT>
-__device__ __forceinline__ void lower_product_mfma(int K, XF xf, YF yf, KR krange, OUT out)
+// Workgroup: the off-diagonal blocks of I = C^-1, whose diagonal blocks hold
+// the inverses of C's already; C's off-diagonal blocks are read.  A wave takes
+// a block column: X_ij = -X_ii sum_{j <= k < i} C_ik X_kj, the sum staying in
+// registers as the second product's operand.
+template <int NW>
+__device__ void inverse_blocks(int nb, const double *C, double *I)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane & 15, kq = lane >> 4;
-    const int nb = (K + 15) / 16;
-    for (int q = wave; q < nb * (nb + 1) / 2; q += NT / 64) {
-        int bi, bj;
-        tri_index(q, bi, bj);
-        int k0, k1;
-        krange(bi, bj, k0, k1);
-        doublex4 acc = doublex4{0.0, 0.0, 0.0, 0.0};
-        for (int kk = k0; kk < k1; kk += 4) {
-            const double a = xf(16 * bi + col, kk + kq);
-            const double b = yf(kk + kq, 16 * bj + col);
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, c = lane & 15;
+    for (int j = wave; j < nb; j += NW)
+        for (int i = j + 1; i < nb; ++i) {
+            // the sum in two chains of products, which wait for each other
+            // less than one would
+            doublex4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+            int k = j;
+            for (; k + 2 <= i; k += 2) {
+                s0 = mul_ab(C + bo(i, k), I + bo(k, j), s0, g, c);
+                s1 = mul_ab(C + bo(i, k + 1), I + bo(k + 1, j), s1, g, c);
+            }
+            if (k < i) s0 = mul_ab(C + bo(i, k), I + bo(k, j), s0, g, c);
+            const double *X = I + bo(i, i);
+            doublex4 r = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = 16 * bi + 4 * v + kq, j = 16 * bj + col;
-            if (i < K && j <= i) out(i, j, acc[v]);
+            for (int v = 0; v < 4; ++v)
+                r = __builtin_amdgcn_mfma_f64_16x16x4f64(-X[c * kBS + 4 * v + g], s0[v] + s1[v], r, 0, 0, 0);
+            store_blk(I + bo(i, j), r, g, c);
+            lds_wave_sync();
         }
+}
+
+// One wave: X = D^-1 of a lower triangular block, lane c the column c.
+__device__ __forceinline__ void tri_inverse_block(const double *D, double *X, int g, int c)
+{
+    double x[16];
+    static_for<0, 16>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        double s = c == r ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < r; ++k) s = fma(-D[r * kBS + k], x[k], s);
+        x[r] = s * rcp_f64(D[r * kBS + r]);
+    });
+    if (g == 0)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) X[r * kBS + c] = x[r];
+}
+
+// y[i] = sum_j M[j][i] x[j] (TRANS) or sum_j M[i][j] x[j], M lower with zeros
+// above the diagonal and x 0 past K, four lanes per entry; out(i, y_i) is
+// called by one of them.
+template <bool TRANS, typename OUT>
+__device__ __forceinline__ void tri_matvec(int K, int nb, const double *M, const double *x, OUT out)
+{
+    const int i = threadIdx.x >> 2, p = threadIdx.x & 3;
+    double s = 0.0;
+    if (i < K) {
+        const int bi = i >> 4, r = i & 15;
+        for (int bj = TRANS ? bi : 0; bj < (TRANS ? nb : bi + 1); ++bj) {
+            const double *m = M + (TRANS ? bo(bj, bi) + r : bo(bi, bj) + r * kBS);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s = fma(m[(4 * q + p) * (TRANS ? kBS : 1)], x[16 * bj + 4 * q + p], s);
+        }
+    }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    if (i < K && p == 0) out(i, s);
+}
+
+// L^-1 (lower, zeros above) to a K x K array, a wave per row.
+template <int NW, typename T>
+__device__ __forceinline__ void store_lower(int K, const double *M, T *out)
+{
+    const int lane = threadIdx.x & 63;
+    for (int r = threadIdx.x >> 6; r < K; r += NW)
+        for (int cc = lane; cc < K; cc += 64) out[r * K + cc] = cc <= r ? (T)M[el(r, cc)] : (T)0;
+}
+
+// Elements (i, j) of the stored blocks of an n x n matrix, dealt to the threads
+// (16 x 16 of them to every NT / 256-th block, consecutive threads along a row
+// of the block, or with ALONG_I along a column, as f's loads are consecutive):
+// all of a thread's values f(i, j) first, so that their loads are in flight
+// together, then stored.
+template <int NT, bool ALONG_I, int U, typename F>
+__device__ __forceinline__ void load_blocks(int nb, double (&x)[U], F f)
+{
+    constexpr int STEP = NT / 256;
+    const int hi = (threadIdx.x >> 4) & 15, lo = threadIdx.x & 15;
+    const int r = ALONG_I ? lo : hi, c = ALONG_I ? hi : lo;
+    int bi = 0, bj = threadIdx.x >> 8;  // block q is (bi, bj)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        while (bj > bi) bj -= ++bi;
+        if (bi < nb) x[u] = f(16 * bi + r, 16 * bj + c);
+        bj += STEP;
     }
 }
 
+template <int NT, bool ALONG_I, int U>
+__device__ __forceinline__ void store_blocks(int nb, double *T, const double (&x)[U])
+{
+    constexpr int STEP = NT / 256;
+    const int hi = (threadIdx.x >> 4) & 15, lo = threadIdx.x & 15;
+    const int at = ALONG_I ? lo * kBS + hi : hi * kBS + lo;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = (threadIdx.x >> 8) + u * STEP;
+        if (q < pk(nb, 0)) T[q * kBlk + at] = x[u];
+    }
+}
+
+constexpr int kMaxBlocks = 8;  // ceil(128 / 16)
+
+// LDS: two block matrices and four vectors.
+size_t draw_lds(int K)
+{
+    const size_t nb = (K + 15) / 16;
+    return sizeof(double) * (nb * (nb + 1) * kBlk + 4 * 16 * nb);
+}
+
+// The K x K algebra in one workgroup.  Bound by its chain: at K = 100 about a
+// third is the seven diagonal factorisations, a quarter the two inversions,
+// the rest loads of fresh sums, products and barriers.  In whole 16 x 16 blocks
+// on the matrix cores, with the noise drawn elsewhere: 10.5 us at K = 10, 16 at
+// 32, 32 at 64, 55 at 100 (packed triangles eliminated two columns a barrier:
+// 20, 46, 115 and 238 us).
 template <int NT, typename T>
 __global__ __launch_bounds__(NT) void hyper_draw(
-    int K, int64_t n, const double *__restrict__ stats, const double *__restrict__ mu0,
-    const double *__restrict__ W0inv, double beta0, double nu0, uint64_t seed, uint32_t stream,
-    const uint32_t *__restrict__ ctr, uint32_t t_off, double *__restrict__ gbuf, int n_lds_bufs,
-    double *__restrict__ mu_out, double *__restrict__ Lam_out, T *__restrict__ Lam_w,
-    T *__restrict__ Lmu_w, T *__restrict__ Linv_w, T *__restrict__ Ltmu_w, int *__restrict__ status)
+    int K, int64_t n, const double *__restrict__ stats, const double *__restrict__ noise,
+    const double *__restrict__ mu0, const double *__restrict__ W0inv, double beta0,
+    double *__restrict__ mu_out, double *__restrict__ Lam_out, T *__restrict__ Lam_w, T *__restrict__ Lmu_w,
+    T *__restrict__ Linv_w, T *__restrict__ Ltmu_w, int *__restrict__ status)
 {
+    constexpr int NW = NT / 64;
     extern __shared__ __align__(16) char smem_raw[];
-    const int KK2 = K * (K + 1) / 2;
-    double *vec = (double *)smem_raw;  // xbar, mu*, z, mu  (4K)
-    double *xbar = vec, *mus = vec + K, *zv = vec + 2 * K, *mu = vec + 3 * K;
-    double *buf[3];
-    for (int q = 0; q < 3; ++q)
-        buf[q] = q < n_lds_bufs ? vec + 4 * K + (size_t)q * KK2 : gbuf + (size_t)q * KK2;
-    double *Cm = buf[0];  // reversed W*^-1, then its Cholesky factor C, then A
-    double *Ci = buf[1];  // C^-1
-    double *Bm = buf[2];  // B = L_W A
+    const int nb = (K + 15) / 16, np = 16 * nb;
+    double *M1 = (double *)smem_raw;  // reversed W*^-1, its factor, A, then B
+    double *M2 = M1 + pk(nb, 0) * kBlk;  // C^-1, then B^-1
+    double *xbar = M2 + pk(nb, 0) * kBlk, *mus = xbar + np, *zv = mus + np, *mu = zv + np;
     __shared__ int ok;
     const int tid = threadIdx.x;
-    const uint32_t t = ctr[0] + t_off;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c = lane & 15;
     const double dn = (double)n;
     const double beta_s = beta0 + dn;
-    const double nu_s = nu0 + dn;
     const double shrink = beta0 * dn / beta_s;
-    if (tid == 0) ok = 1;
-    for (int k = tid; k < K; k += NT) {
-        xbar[k] = stats[k] / dn;
-        mus[k] = (beta0 * mu0[k] + dn * xbar[k]) / beta_s;
-    }
-    __syncthreads();
-    // J W*^-1 J, packed: entry (i, j), i >= j, is W*^-1[K-1-j][K-1-i]
-    for (int e = tid; e < KK2; e += NT) {
-        int a, b;
-        tri_index(e, a, b);  // W*^-1 entry (a, b), a >= b
-        const double S = stats[K + e] - dn * xbar[a] * xbar[b];
-        const double w = W0inv[a * K + b] + S + shrink * (xbar[a] - mu0[a]) * (xbar[b] - mu0[b]);
-        Cm[pk(K - 1 - b, K - 1 - a)] = w;
-    }
-    __syncthreads();
-    chol_packed<NT>(K, Cm, &ok);
-    tri_inverse_packed<NT>(K, Cm, Ci);
-    // Bartlett factor A (reuses Cm)
-    for (int e = tid; e < KK2; e += NT) Cm[e] = 0.0;
-    __syncthreads();
-    for (int k = tid; k < K; k += NT)
-        Cm[pk(k, k)] = sqrt(chi_square(seed, stream, t, (uint32_t)k, nu_s - (double)k, &ok));
     const int n_low = K * (K - 1) / 2;
-    for (int blk = tid; 4 * blk < n_low; blk += NT) {
-        double z[4];
-        normals_block(seed, (uint32_t)blk, t, stream, 1u, 0u, z);
-        for (int l = 0; l < 4 && 4 * blk + l < n_low; ++l) {
-            int r, c;
-            tri_index(4 * blk + l, r, c);  // strict-lower row-major index = pk(r+1, c)
-            Cm[pk(r + 1, c)] = z[l];
-        }
+    if (tid == 0) ok = 1;
+    for (int k = tid; k < np; k += NT) {
+        const int kk = min(k, K - 1);
+        const double xb = stats[kk] / dn, m0 = mu0[kk];
+        xbar[k] = k < K ? xb : 0.0;
+        mu[k] = k < K ? xb - m0 : 0.0;
+        mus[k] = k < K ? (beta0 * m0 + dn * xb) / beta_s : 0.0;
+        zv[k] = k < K ? noise[n_low + kk] : 0.0;
     }
+    // the Bartlett factor A (the identity on the padding), read ahead of its use
+    constexpr int kFill = NT == 256 ? 10 : kMaxBlocks * (kMaxBlocks + 1) / 4;
+    double areg[kFill];
+    load_blocks<NT, false>(nb, areg, [&](int i, int j) {
+        const int ii = min(i, K - 1);
+        const double z = noise[i == j ? n_low + K + ii : (j < ii ? pk(ii - 1, j) : 0)];  // a load without a branch
+        return i < K ? (j <= i ? z : 0.0) : (i == j ? 1.0 : 0.0);
+    });
     __syncthreads();
-    // B = L_W A, L_W[r][m] = C^-1[K-1-m][K-1-r] (lower), A lower: block
-    // (bi, bj) sums m over blocks bj .. bi
-    lower_product_mfma<NT>(
-        K, [&](int r, int m) { return (r < K && m <= r) ? Ci[pk(K - 1 - m, K - 1 - r)] : 0.0; },
-        [&](int m, int c) { return (m < K && c <= m) ? Cm[pk(m, c)] : 0.0; },
-        [](int bi, int bj, int &k0, int &k1) {
-            k0 = 16 * bj;
-            k1 = 16 * bi + 16;
-        },
-        [&](int r, int c, double d) { Bm[pk(r, c)] = d; });
-    __syncthreads();
-    // Lambda = B B^T: block (bi, bj) sums m over blocks 0 .. bj
-    lower_product_mfma<NT>(
-        K, [&](int r, int m) { return (r < K && m <= r) ? Bm[pk(r, m)] : 0.0; },
-        [&](int m, int c) { return (c < K && m <= c) ? Bm[pk(c, m)] : 0.0; },
-        [](int bi, int bj, int &k0, int &k1) {
-            k0 = 0;
-            k1 = 16 * bj + 16;
-        },
-        [&](int r, int c, double d) {
-            Lam_out[r * K + c] = d;
-            Lam_out[c * K + r] = d;
-            Lam_w[r * K + c] = (T)d;
-            Lam_w[c * K + r] = (T)d;
+    // J W*^-1 J over the padded order: entry (i, j) is W*^-1[np-1-j][np-1-i]
+    {
+        double w[kFill];
+        load_blocks<NT, true>(nb, w, [&](int i, int j) {
+            const int a = np - 1 - min(i, j), b = np - 1 - max(i, j);  // a >= b
+            const int aa = min(a, K - 1), bb = min(b, K - 1);          // loads without a branch
+            const double S = stats[K + pk(aa, bb)] - dn * xbar[aa] * xbar[bb];
+            const double x = W0inv[aa * K + bb] + S + shrink * mu[aa] * mu[bb];  // mu: xbar - mu0
+            return a < K ? x : (i == j ? 1.0 : 0.0);
         });
-    for (int blk = tid; 4 * blk < K; blk += NT) {
-        double z[4];
-        normals_block(seed, (uint32_t)blk, t, stream, 2u, 0u, z);
-        for (int l = 0; l < 4 && 4 * blk + l < K; ++l) zv[4 * blk + l] = z[l];
+        store_blocks<NT, true>(nb, M1, w);
     }
     __syncthreads();
-    if (Linv_w) {
-        // the rank-one row path needs B^-1 anyway: x = B^-T z as a product
-        tri_inverse_packed<NT>(K, Bm, Ci);
-        for (int i = tid; i < K; i += NT) {
-            double s = 0.0;
-            for (int j = i; j < K; ++j) s += Ci[pk(j, i)] * zv[j];
-            mu[i] = s;  // staged: zv is still being read
+    chol_blocks<NW>(nb, M1, &ok);
+    for (int b = wave; b < nb; b += NW) store_blk(M2 + bo(b, b), load_blk(M1 + bo(b, b), g, c), g, c);
+    __syncthreads();
+    inverse_blocks<NW>(nb, M1, M2);
+    __syncthreads();
+    store_blocks<NT, false>(nb, M1, areg);
+    __syncthreads();
+    // B = L_W A, L_W[r][m] = C^-1[np-1-m][np-1-r]; kept in registers until every
+    // wave has read A
+    {
+        constexpr int kMine = (NT == 256 ? 10 : kMaxBlocks * (kMaxBlocks + 1) / 2) / NW + 1;
+        doublex4 acc[kMine];
+#pragma unroll
+        for (int m = 0; m < kMine; ++m) {
+            const int q = wave + m * NW;
+            if (q >= pk(nb, 0)) break;
+            int bi, bj;
+            tri_index(q, bi, bj);
+            acc[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+            for (int bm = bj; bm <= bi; ++bm) {
+                const double *Cb = M2 + bo(nb - 1 - bm, nb - 1 - bi), *Ab = M1 + bo(bm, bj);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(Cb[(15 - 4 * s - g) * kBS + 15 - c],
+                                                                  Ab[(4 * s + g) * kBS + c], acc[m], 0, 0, 0);
+            }
         }
         __syncthreads();
-        for (int i = tid; i < K; i += NT) zv[i] = mu[i];
-    } else {
-        // x = B^-T z (column oriented, one barrier per step), in zv: step i
-        // takes x_i = zv[i] / B[i][i] (zv[i] final) and updates zv[j], j < i;
-        // the divisions are applied to zv at the end
-        for (int i = K - 1; i > 0; --i) {
-            const double xi = zv[i] / Bm[pk(i, i)];
-            for (int j = tid; j < i; j += NT) zv[j] -= Bm[pk(i, j)] * xi;
-            __syncthreads();
+#pragma unroll
+        for (int m = 0; m < kMine; ++m) {
+            const int q = wave + m * NW;
+            if (q < pk(nb, 0)) store_blk(M1 + q * kBlk, acc[m], g, c);
         }
-        for (int i = tid; i < K; i += NT) zv[i] /= Bm[pk(i, i)];
+    }
+    __syncthreads();
+    // B^-1 into M2 (block columns by wave), then Lambda = B B^T
+    for (int b = wave; b < nb; b += NW) tri_inverse_block(M1 + bo(b, b), M2 + bo(b, b), g, c);
+    __syncthreads();
+    inverse_blocks<NW>(nb, M1, M2);
+    for (int q = NW - 1 - wave; q < pk(nb, 0); q += NW) {  // the last waves have the shortest columns above
+        int bi, bj;
+        tri_index(q, bi, bj);
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int bm = 0; bm <= bj; ++bm) acc = mul_abt(M1 + bo(bi, bm), M1 + bo(bj, bm), 1.0, acc, g, c);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * bi + 4 * v + g, j = 16 * bj + c;
+            if (i < K && j <= i) {
+                Lam_out[i * K + j] = acc[v];
+                Lam_out[j * K + i] = acc[v];
+                Lam_w[i * K + j] = (T)acc[v];
+                Lam_w[j * K + i] = (T)acc[v];
+            }
+        }
     }
     __syncthreads();
     const double rs = 1.0 / sqrt(beta_s);
-    for (int k = tid; k < K; k += NT) {
-        mu[k] = mus[k] + zv[k] * rs;
-        mu_out[k] = mu[k];
-    }
+    tri_matvec<true>(K, nb, M2, zv, [&](int i, double x) {
+        mu[i] = mus[i] + x * rs;
+        mu_out[i] = mu[i];
+    });
     __syncthreads();
-    // Lambda mu from the packed factor: Lambda mu = B (B^T mu)
-    for (int i = tid; i < K; i += NT) {
-        double s = 0.0;
-        for (int j = i; j < K; ++j) s += Bm[pk(j, i)] * mu[j];
-        zv[i] = s;  // B^T mu
-    }
+    // Lambda mu = B (B^T mu)
+    tri_matvec<true>(K, nb, M1, mu, [&](int i, double x) { xbar[i] = x; });  // xbar and mu stay 0 past K
     __syncthreads();
-    for (int i = tid; i < K; i += NT) {
-        double s = 0.0;
-        for (int j = 0; j <= i; ++j) s += Bm[pk(i, j)] * zv[j];
-        Lmu_w[i] = (T)s;
-    }
+    tri_matvec<false>(K, nb, M1, xbar, [&](int i, double x) { Lmu_w[i] = (T)x; });
     if (Linv_w) {
-        // for the rank-one row path: chol(Lambda)^-1 = B^-1 (in Ci since the
-        // solve for mu) and B^T mu
-        for (int i = tid; i < K; i += NT) Ltmu_w[i] = (T)zv[i];
-        for (int e = tid; e < K * K; e += NT) {
-            const int r = e / K, cc = e - (e / K) * K;
-            Linv_w[e] = cc <= r ? (T)Ci[pk(r, cc)] : (T)0;
-        }
+        // for the rank-one row path: chol(Lambda)^-1 = B^-1 and B^T mu
+        for (int i = tid; i < K; i += NT) Ltmu_w[i] = (T)xbar[i];
+        store_lower<NW>(K, M2, Linv_w);
     }
     if (tid == 0 && !ok) *status = 0;
 }
 
-// For the rank-one row path after (mu, Lambda) were set by the host:
-// chol(Lambda)^-1 and chol(Lambda)^T mu, FP64 in one workgroup.
+// For the rank-one row path (K <= 64) after (mu, Lambda) were set by the host:
+// L^-1 and L^T mu = L^-1 (Lambda mu), L = chol(Lambda), FP64 in one workgroup.
 template <typename T>
-__global__ __launch_bounds__(kDrawThreads) void prior_factor(int K, const double *__restrict__ mu,
-                                                         const double *__restrict__ Lam,
-                                                         T *__restrict__ Linv_w, T *__restrict__ Ltmu_w,
-                                                         int *__restrict__ status)
+__global__ __launch_bounds__(256) void prior_factor(int K, const double *__restrict__ mu,
+                                                    const double *__restrict__ Lam, T *__restrict__ Linv_w,
+                                                    T *__restrict__ Ltmu_w, int *__restrict__ status)
 {
     extern __shared__ __align__(16) char smem_raw[];
-    const int KK2 = K * (K + 1) / 2;
-    double *P = (double *)smem_raw;
-    double *Ci = P + KK2;
+    const int nb = (K + 15) / 16;
+    double *M1 = (double *)smem_raw, *M2 = M1 + pk(nb, 0) * kBlk, *lm = M2 + pk(nb, 0) * kBlk;
     __shared__ int ok;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c = lane & 15;
     if (tid == 0) ok = 1;
-    for (int e = tid; e < KK2; e += kDrawThreads) {
-        int r, c;
-        tri_index(e, r, c);
-        P[e] = Lam[r * K + c];
+    double w[10];
+    load_blocks<256, false>(nb, w, [&](int i, int j) {
+        const int a = max(i, j), b = min(i, j);  // the lower triangle
+        return a < K ? Lam[a * K + b] : (i == j ? 1.0 : 0.0);
+    });
+    store_blocks<256, false>(nb, M1, w);
+    for (int i = tid; i < 16 * nb; i += 256) {
+        double s = 0.0;
+        for (int j = 0; i < K && j < K; ++j) s += Lam[i >= j ? i * K + j : j * K + i] * mu[j];
+        lm[i] = s;
     }
     __syncthreads();
-    chol_packed<kDrawThreads>(K, P, &ok);
-    tri_inverse_packed<kDrawThreads>(K, P, Ci);
-    for (int e = tid; e < K * K; e += kDrawThreads) {
-        const int r = e / K, cc = e - (e / K) * K;
-        Linv_w[e] = cc <= r ? (T)Ci[pk(r, cc)] : (T)0;
-    }
-    for (int i = tid; i < K; i += kDrawThreads) {
-        double s = 0.0;
-        for (int j = i; j < K; ++j) s += P[pk(j, i)] * mu[j];
-        Ltmu_w[i] = (T)s;
-    }
+    chol_blocks<4>(nb, M1, &ok);
+    for (int b = wave; b < nb; b += 4) store_blk(M2 + bo(b, b), load_blk(M1 + bo(b, b), g, c), g, c);
+    __syncthreads();
+    inverse_blocks<4>(nb, M1, M2);
+    __syncthreads();
+    store_lower<4>(K, M2, Linv_w);
+    tri_matvec<false>(K, nb, M2, lm, [&](int i, double x) { Ltmu_w[i] = (T)x; });
     if (tid == 0 && !ok) *status = 0;
 }
 
@@ -562,129 +773,84 @@ __global__ void prior_to_working(int K, const double *__restrict__ mu, const dou
     for (int q = tid; q < K * K; q += blockDim.x) Lam_w[q] = (T)Lam[q];
 }
 
-template <int NE>
-void launch_moments(bpmf_ctx *c, const Side &sd, double *part, int used, int64_t chunk, hipStream_t s)
-{
-    const int tile_rows = (int)std::min<size_t>(64, 49152 / (sizeof(double) * (c->K + 1)));
-    const size_t lds = sizeof(double) * tile_rows * (c->K + 1);
-    if (c->prec == 0)
-        hipLaunchKernelGGL((hyper_moments<NE, double>), dim3(used), dim3(kThreads), lds, s, c->K,
-                           (const double *)sd.X, c->ld, sd.rows, chunk, tile_rows, part);
-    else
-        hipLaunchKernelGGL((hyper_moments<NE, float>), dim3(used), dim3(kThreads), lds, s, c->K,
-                           (const float *)sd.X, c->ld, sd.rows, chunk, tile_rows, part);
-}
-
-int lds_buffers(int K, int lds_max)
-{
-    const size_t KK2 = (size_t)K * (K + 1) / 2;
-    const size_t base = sizeof(double) * 4 * (size_t)K;
-    int nb = 3;
-    while (nb > 0 && base + sizeof(double) * nb * KK2 > (size_t)lds_max) --nb;
-    return nb;
-}
-
-size_t draw_lds(int K, int nb) { return sizeof(double) * (4 * (size_t)K + nb * (size_t)K * (K + 1) / 2); }
-
 }  // namespace
 
 hipError_t launch_hyper(bpmf_ctx *c, int side_id, hipStream_t s, uint32_t t_off)
 {
     double *part = c->hyp_part[side_id], *stats = c->hyp_stats[side_id];
-    double *scratch = c->hyp_scratch[side_id];
+    double *noise = c->hyp_noise[side_id];
     Side &sd = c->side[side_id];
     const int K = c->K;
     const int E = K + K * (K + 1) / 2;
     const int64_t rows = sd.rows;
-    const int nblk = c->hyp_blocks;
-    int64_t chunk = (rows + nblk - 1) / nblk;
-    if (chunk < 1) chunk = 1;
-    int used = (int)((rows + chunk - 1) / chunk);
-    if (used < 1) used = 1;
-    const int nbk = (K + 15) / 16;
-    if (nbk <= 7) {
-        auto go = [&](auto nbc) {
-            constexpr int NB = decltype(nbc)::value;
-            if (c->prec == 0)
-                hipLaunchKernelGGL((hyper_moments_mfma<NB, double>), dim3(used), dim3(64), 0, s, K,
-                                   (const double *)sd.X, c->ld, rows, chunk, part);
-            else
-                hipLaunchKernelGGL((hyper_moments_mfma<NB, float>), dim3(used), dim3(64), 0, s, K,
-                                   (const float *)sd.X, c->ld, rows, chunk, part);
+    // rows a wave: at least 16, with fewer the reduction reads more than the
+    // moments did
+    const int64_t waves = (int64_t)c->hyp_blocks * kMomentsWaves;
+    const int64_t chunk = std::max<int64_t>(16, (rows + waves - 1) / waves);
+    const int used = (int)((rows + chunk * kMomentsWaves - 1) / (chunk * kMomentsWaves));
+    auto moments = [&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        auto go = [&](auto kern, auto *X) {
+            hipLaunchKernelGGL(kern, dim3(used), dim3(64 * kMomentsWaves), 0, s, K, X, c->ld, rows, chunk, part);
         };
-        switch (nbk) {
-        case 1: go(std::integral_constant<int, 1>{}); break;
-        case 2: go(std::integral_constant<int, 2>{}); break;
-        case 3: go(std::integral_constant<int, 3>{}); break;
-        case 4: go(std::integral_constant<int, 4>{}); break;
-        case 5: go(std::integral_constant<int, 5>{}); break;
-        case 6: go(std::integral_constant<int, 6>{}); break;
-        default: go(std::integral_constant<int, 7>{}); break;
+        if constexpr (NB <= 4) {
+            if (c->prec == 0)
+                go(hyper_moments_mfma<NB, double>, (const double *)sd.X);
+            else
+                go(hyper_moments_mfma<NB, float>, (const float *)sd.X);
+        } else {  // FP64 factors stop at K = 64
+            go(hyper_moments_wide<NB, float>, (const float *)sd.X);
         }
-    } else {
-        const int ne = (E + kThreads - 1) / kThreads;
-        if (ne <= 3) launch_moments<3>(c, sd, part, used, chunk, s);
-        else if (ne <= 9) launch_moments<9>(c, sd, part, used, chunk, s);
-        else if (ne <= 21) launch_moments<21>(c, sd, part, used, chunk, s);
-        else launch_moments<33>(c, sd, part, used, chunk, s);
+    };
+    switch ((K + 15) / 16) {
+    case 1: moments(std::integral_constant<int, 1>{}); break;
+    case 2: moments(std::integral_constant<int, 2>{}); break;
+    case 3: moments(std::integral_constant<int, 3>{}); break;
+    case 4: moments(std::integral_constant<int, 4>{}); break;
+    case 5: moments(std::integral_constant<int, 5>{}); break;
+    case 6: moments(std::integral_constant<int, 6>{}); break;
+    case 7: moments(std::integral_constant<int, 7>{}); break;
+    default: moments(std::integral_constant<int, 8>{}); break;
     }
-    double *red = c->hyp_red[side_id];
-    hipLaunchKernelGGL(hyper_reduce_groups, dim3((E + 63) / 64, kRedGroups), dim3(64), 0, s, E, used, part, red);
-    hipLaunchKernelGGL(hyper_reduce, dim3((E + 63) / 64), dim3(64), 0, s, E, (const double *)red, stats);
-    const int nb = lds_buffers(K, c->hyp_lds_max);
-    const size_t lds2 = draw_lds(K, nb);
-    // K <= 64: 256 threads (four waves find room beside the other side's row
-    // kernels, where a 1024-thread workgroup waits for a whole free CU; one
-    // wave is slower again: the steps' work outweighs their barriers);
-    // above, 1024 threads
+    const int groups = (E + 15) / 16;
+    const int jobs = (K * (K - 1) / 2 + 3) / 4 + (K + 3) / 4 + K;
+    hipLaunchKernelGGL(hyper_reduce, dim3(groups + (jobs + kRedThreads - 1) / kRedThreads), dim3(kRedThreads), 0, s,
+                       K, used, (const double *)part, stats, groups, c->nu0 + (double)rows, c->seed, sd.stream_hyp,
+                       c->ctr, t_off, noise, c->hyp_status);
+    const size_t lds = draw_lds(K);
+    // K <= 64: four waves (at most four block columns), which find room beside
+    // the other side's row kernels; above, eight
     auto draw = [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
         if (c->prec == 0)
-            hipLaunchKernelGGL((hyper_draw<NT, double>), dim3(1), dim3(NT), lds2, s, K, rows, stats, c->d_mu0,
-                               c->d_W0inv, c->beta0, c->nu0, c->seed, sd.stream_hyp, c->ctr, t_off, scratch, nb,
-                               sd.mu, sd.Lam, (double *)sd.Lam_w, (double *)sd.Lmu_w, (double *)nullptr,
-                               (double *)nullptr, c->hyp_status);
+            hipLaunchKernelGGL((hyper_draw<NT, double>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
+                               c->d_W0inv, c->beta0, sd.mu, sd.Lam, (double *)sd.Lam_w, (double *)sd.Lmu_w,
+                               (double *)nullptr, (double *)nullptr, c->hyp_status);
         else
-            hipLaunchKernelGGL((hyper_draw<NT, float>), dim3(1), dim3(NT), lds2, s, K, rows, stats, c->d_mu0,
-                               c->d_W0inv, c->beta0, c->nu0, c->seed, sd.stream_hyp, c->ctr, t_off, scratch, nb,
-                               sd.mu, sd.Lam, (float *)sd.Lam_w, (float *)sd.Lmu_w,
+            hipLaunchKernelGGL((hyper_draw<NT, float>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
+                               c->d_W0inv, c->beta0, sd.mu, sd.Lam, (float *)sd.Lam_w, (float *)sd.Lmu_w,
                                sd.n_low ? (float *)sd.Linv_w : (float *)nullptr,
                                sd.n_low ? (float *)sd.Ltmu_w : (float *)nullptr, c->hyp_status);
     };
     if (K <= 64)
         draw(std::integral_constant<int, 256>{});
     else
-        draw(std::integral_constant<int, kDrawThreads>{});
+        draw(std::integral_constant<int, 512>{});
     return hipGetLastError();
 }
 
 hipError_t prepare_hyper(bpmf_ctx *c)
 {
-    int dev_max = 65536;
-    hipError_t e = hipDeviceGetAttribute(&dev_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device);
-    if (e != hipSuccess) return e;
-    c->hyp_lds_max = dev_max;
-    const size_t need = draw_lds(c->K, lds_buffers(c->K, dev_max));
-    if (need > 65536) {  // only above K = 64, where the draw has 1024 threads
-        e = hipFuncSetAttribute((const void *)hyper_draw<kDrawThreads, double>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)hyper_draw<kDrawThreads, float>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-        if (e != hipSuccess) {  // keep the draw within the default limit
-            (void)hipGetLastError();
-            c->hyp_lds_max = 65536;
-        }
-    }
-    return hipSuccess;
+    const int need = (int)draw_lds(c->K);
+    if (need <= 65536) return hipSuccess;  // only above K = 64 (FP32 factors, 512 threads)
+    return hipFuncSetAttribute((const void *)hyper_draw<512, float>, hipFuncAttributeMaxDynamicSharedMemorySize, need);
 }
 
 hipError_t launch_prior_to_working(bpmf_ctx *c, int side_id, hipStream_t s)
 {
     Side &sd = c->side[side_id];
     if (sd.n_low && c->prec == 1) {
-        const size_t lds = sizeof(double) * (size_t)c->K * (c->K + 1);
-        hipLaunchKernelGGL((prior_factor<float>), dim3(1), dim3(kDrawThreads), lds, s, c->K, sd.mu, sd.Lam,
+        hipLaunchKernelGGL((prior_factor<float>), dim3(1), dim3(256), draw_lds(c->K), s, c->K, sd.mu, sd.Lam,
                            (float *)sd.Linv_w, (float *)sd.Ltmu_w, c->hyp_status);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

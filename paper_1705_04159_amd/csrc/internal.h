@@ -117,15 +117,13 @@ struct bpmf_ctx {
     int64_t hist_cap = 0;
     // hyper workspace, one set per side so that the two draws may overlap
     double *hyp_part[2] = {};     // [hyp_blocks * (K + K(K+1)/2)]
-    double *hyp_red[2] = {};      // [kHypRedGroups * (K + K(K+1)/2)] sums of the reduction's first pass
     int hyp_blocks = 0;
     double *hyp_stats[2] = {};    // [K + K(K+1)/2]
-    double *hyp_scratch[2] = {};  // [4 * K * K + 8 * K]
+    double *hyp_noise[2] = {};    // [K (K - 1) / 2 + 2 K] noise of the draw
     // flags, 1 = ok: [0] hyper draw, [1] row draws (pivots); pinned coherent host
     // memory that kernels clear in place, so that reading them after a
     // call's one synchronisation costs no copy
     int *hyp_status = nullptr;
-    int hyp_lds_max = 65536;      // LDS bytes the draw kernel may use
     // split partials
     void *part = nullptr;
     int64_t part_slots = 0;
