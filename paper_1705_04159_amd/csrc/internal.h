@@ -52,7 +52,7 @@ enum UpdateStage { kStagePrior = 0, kStageSegments = 1, kStageRows = 2, kStageFi
 struct Side {
     int64_t rows = 0;
     int64_t *ptr = nullptr;  // device [rows + 1] neighbour offsets
-    int32_t *nbr = nullptr;  // device [nnz] neighbour ids (other side)
+    int32_t *nbr = nullptr;  // device [nnz + 32] neighbour ids (other side), ending in 32 zeros
     void *rc = nullptr;      // device [nnz] centred ratings (float, or double in FP64 mode)
     void *X = nullptr;       // device [rows * ld] factor
     uint16_t *Xbf = nullptr; // device [rows * ld] BF16 copy of the factor (BF16 mode)
@@ -166,6 +166,38 @@ struct bpmf_ctx {
 };
 
 namespace bpmf {
+
+// Ratings above which a work item's Gram is dealt to the four waves of a
+// workgroup.  The workload model of Sec. IV-B: a row costs 3K + d rating
+// equivalents (measured at K = 32 and 100), and with W their sum over the side
+// and `in_flight` waves on the GPU a row of d alone on its wave prolongs the
+// launch once (3K + d) in_flight / W exceeds about one half.  Dealing costs
+// throughput (three of four waves end before the factorisation: at K = 100,
+// 60,024 users with 11.3 M ratings, a limit of 512 instead of 2048 takes the
+// users' update from 1336 to 1382 us), so nothing shorter is dealt, and at
+// least 256 ratings, which is two chunks a wave.
+inline int64_t heavy_limit(const Side &sd, int64_t nnz, int K, int64_t in_flight)
+{
+    const int64_t W = 3 * (int64_t)K * (sd.rows - sd.n_low) + nnz;
+    const int64_t d = W / (2 * in_flight) - 3 * (int64_t)K;
+    return d > 256 ? d : 256;
+}
+
+// Whole rows of a side with more than `ratings` ratings: the first of its
+// whole-row work items (degrees descend).
+inline int64_t whole_rows_above(const Side &sd, int64_t ratings)
+{
+    int64_t lo = sd.n_split, hi = sd.rows - sd.n_low;
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        const int32_t r = sd.perm[mid];
+        if (sd.hptr[r + 1] - sd.hptr[r] > ratings)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo - sd.n_split;
+}
 
 // ---- launchers (defined in the .hip files; all enqueue on `s`) ----
 // Row update of one side: items, then split-row finishes.

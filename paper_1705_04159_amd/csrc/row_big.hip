@@ -4,7 +4,7 @@
 // Per row (Algorithm 1's item body with BPMF's conditional):
 //   P = Lambda + alpha sum_j y_j y_j^T,  b = Lambda mu + alpha sum_j r'_j y_j,
 //   P = L L^T,  y = L^-1 b,  x = L^-T (y + z).
-// One wavefront per work item.
+// One wavefront per work item, four for the Gram of a heavy one.
 //
 // Gram: FP32 rows on v_mfma_f32_16x16x4_f32 (as for K <= 32), or -- in the
 // BF16-Gram mode -- BF16 copies of the neighbour rows on
@@ -40,6 +40,8 @@
 //
 // Noise as in the other row kernels: Philox4x32-10 normal c of the row from
 // block c/4 of counter (row, t, stream<<24 | block, 0), Box-Muller in FP32.
+#include <algorithm>
+
 #include "internal.h"
 #include "rng_device.h"
 #include "row_common.h"
@@ -50,8 +52,8 @@ namespace bpmf {
 namespace {
 
 
-constexpr int kBigWPB = 1;     // waves per workgroup (independent; one-wave groups measured best)
-constexpr int kPS = 17;        // panel row stride (floats)
+constexpr int kWaves = 4;      // waves per workgroup of row_big
+constexpr int64_t kSimds = 1024;
 
 // Waves per SIMD the register allocation must allow (left alone, the
 // compiler trades occupancy for unrolled loads and drops to one wave).
@@ -69,6 +71,8 @@ struct BigLds {
     static constexpr int VEC = 16 * NB;
     static constexpr int BV = XS;  // offset of b
     static constexpr int TOTAL = XS + 3 * VEC;
+    static constexpr int SUM = 64 * (4 * (NB * (NB + 1) / 2) + NB);  // one wave's accumulators and rhs
+    static constexpr int GROUP = kWaves * TOTAL > SUM ? kWaves * TOTAL : SUM;  // floats of a workgroup
 };
 
 __device__ __forceinline__ void wave_sync()
@@ -105,7 +109,7 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
                                                float (&bacc)[NB])
 {
     const uint32_t cnt = (uint32_t)(it.end - it.beg);
-    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, cnt * 4u);
+    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, (cnt + 32u) * 4u);
     const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(rc + it.beg, AUG ? 0u : cnt * 4u);
     // the three planes from this item on, one descriptor; lane part p reads
     // plane p, the other lanes read nothing
@@ -117,28 +121,27 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
     const bool pad_lane = col >= kr;  // components >= K of the last block
     const uint32_t coff = 2u * col;
     const uint32_t nchunk = (cnt + 31) / 32;
+    uint32_t jb[8];
+    auto load_ids = [&](uint32_t ch) { buf_ids8(jsrc, (ch * 32 + 8 * kq) * 4u, jb); };
     // the first chunk starts the accumulators from zero (no separate clear)
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
-        uint32_t base[8];
         float r[8];
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t t = ch * 32 + 8 * kq + e;
-            const uint32_t j = buf_u32_stream(jsrc, t * 4u);
-            if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            base[e] = __umul24(j, ldy2) + coff;  // fewer than 2^24 rows
-            if (last) base[e] = t < cnt ? base[e] : kOOB;
-        }
-        u32x4 rp = u32x4{0u, 0u, 0u, 0u};
-        if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, 0);
         // raw BF16 bits; pairs packed into dwords form the MFMA operand
         uint32_t yr[NB][8];
 #pragma unroll
-        for (int bi = 0; bi < NB; ++bi)
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t t = ch * 32 + 8 * kq + e;
+            if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
+            uint32_t base = __umul24(jb[e], ldy2) + coff;  // fewer than 2^24 rows
+            if (last) base = t < cnt ? base : kOOB;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) yr[bi][e] = buf_u16(ysrc, base[e] + 32u * bi) & 0xFFFFu;
+            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_u16(ysrc, base + 32u * bi) & 0xFFFFu;
+        }
+        u32x4 rp = u32x4{0u, 0u, 0u, 0u};
+        if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, 0);
+        if (!last) load_ids(ch + 1);
         bf16x8 y[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
@@ -169,6 +172,7 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
         }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
+    load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -196,7 +200,7 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
                                               floatx4 (&acc)[NB * (NB + 1) / 2], float (&bacc)[NB])
 {
     const uint32_t cnt = (uint32_t)(it.end - it.beg);
-    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, cnt * 4u);
+    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, (cnt + 32u) * 4u);
     const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(rc + it.beg, AUG ? 0u : cnt * 4u);
     const int p = col - kr;
     const bool part_lane = p >= 0 && p < 3;
@@ -206,27 +210,30 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
     const bool pad_lane = col >= kr;  // components >= K of the last block
     const uint32_t coff = 4u * col;
     const uint32_t nchunk = (cnt + 31) / 32;
+    uint32_t jb[8];
+    auto load_ids = [&](uint32_t ch) { buf_ids8(jsrc, (ch * 32 + 8 * kq) * 4u, jb); };
+    // a chunk's rows are loaded together, into the registers that the parts
+    // of the chunk before have left, and the next chunk's ids behind them
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
-        uint32_t base[8];
-        float r[8];
+        float r[8], yr[NB][8];
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const uint32_t t = ch * 32 + 8 * kq + e;
-            const uint32_t j = buf_u32_stream(jsrc, t * 4u);
             if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            base[e] = __umul24(j, ldy4) + coff;  // fewer than 2^24 rows
-            if (last) base[e] = t < cnt ? base[e] : kOOB;
+            uint32_t base = __umul24(jb[e], ldy4) + coff;  // fewer than 2^24 rows
+            if (last) base = t < cnt ? base : kOOB;
+#pragma unroll
+            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_f32(ysrc, base + 64u * bi);
         }
         u32x4 rp = u32x4{0u, 0u, 0u, 0u};
         if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, kStreamPolicy);
+        if (!last) load_ids(ch + 1);
         bf16x8 H[NB], M[NB], L[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
-            float yv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) yv[e] = buf_f32(ysrc, base[e] + 64u * bi);
+            const float (&yv)[8] = yr[bi];
             if constexpr (!AUG) {
                 float s = 0.f;
 #pragma unroll
@@ -269,6 +276,7 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
             }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
+    load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -545,9 +553,12 @@ constexpr int64_t big_slot_elems()
 // factorisation's budget.)  AUG (BF16 rows with K - 16 (NB - 1) <= 13): the
 // rhs comes out of the Gram, the rating parts being padding components;
 // otherwise it is summed on the vector units.
+// Workgroups [0, n_heavy) take one heavy item each (the four waves a quarter
+// of its ratings, summed in wave order from the last), the others one item a
+// wave.
 template <int NB, bool BF16, bool SEG, bool AUG>
-__global__ __launch_bounds__(64 * kBigWPB, big_waves<NB>()) void row_big(
-    int K, float alpha, const RowItem *__restrict__ items, int64_t item0, int64_t n_items,
+__global__ __launch_bounds__(64 * kWaves, big_waves<NB>()) void row_big(
+    int K, float alpha, const RowItem *__restrict__ items, int64_t item0, int64_t n_heavy, int64_t n_items,
     const int32_t *__restrict__ nbr, const float *__restrict__ rc, const uint16_t *__restrict__ rc3,
     uint32_t plane, const void *__restrict__ Y, int ldy, uint32_t y_bytes, const floatx4 *__restrict__ img,
     const float *__restrict__ Lmu, float *__restrict__ X, int ldx, float *__restrict__ part, uint64_t seed,
@@ -557,19 +568,50 @@ __global__ __launch_bounds__(64 * kBigWPB, big_waves<NB>()) void row_big(
     extern __shared__ float smem_f[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const int64_t id = item0 + (int64_t)blockIdx.x * kBigWPB + wave;
+    const bool heavy = (int64_t)blockIdx.x < n_heavy;
+    const int64_t id = item0 + (heavy ? (int64_t)blockIdx.x
+                                      : n_heavy + ((int64_t)blockIdx.x - n_heavy) * kWaves + wave);
     if (id >= n_items) return;
     const int col = lane & 15;
     const int kq = lane >> 4;
     const int kr = K - 16 * (NB - 1);  // real components of the last block
     const RowItem it = items[id];
+    RowItem mine = it;
+    if (heavy) {  // whole chunks of 32 to each wave
+        const int64_t per = (it.end - it.beg + 32 * kWaves - 1) / (32 * kWaves) * 32;
+        mine.beg = min<int64_t>(it.end, it.beg + wave * per);
+        mine.end = min<int64_t>(it.end, mine.beg + per);
+    }
     const __amdgpu_buffer_rsrc_t ysrc = make_rsrc(Y, y_bytes);
     floatx4 acc[NBLK];
     float bacc[NB];
     if constexpr (BF16)
-        gram_item_bf16<NB, AUG>(it, nbr, rc, rc3, plane, kr, ysrc, (uint32_t)ldy * 2u, kq, col, acc, bacc);
+        gram_item_bf16<NB, AUG>(mine, nbr, rc, rc3, plane, kr, ysrc, (uint32_t)ldy * 2u, kq, col, acc, bacc);
     else  // FP32 rows: the Gram from their three-part BF16 splits
-        gram_item_p3t<NB, AUG>(it, nbr, rc, rc3, plane, kr, ysrc, (uint32_t)ldy * 4u, kq, col, acc, bacc);
+        gram_item_p3t<NB, AUG>(mine, nbr, rc, rc3, plane, kr, ysrc, (uint32_t)ldy * 4u, kq, col, acc, bacc);
+    if (heavy) {
+        floatx4 *sa = reinterpret_cast<floatx4 *>(smem_f);
+        float *sb = smem_f + NBLK * 256;
+        for (int w = kWaves - 1; w > 0; --w) {
+            if (wave == w) {
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q) sa[64 * q + lane] = acc[q];
+                if constexpr (!AUG)
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) sb[64 * bi + lane] = bacc[bi];
+            }
+            __syncthreads();
+            if (wave == w - 1) {
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q) acc[q] += sa[64 * q + lane];
+                if constexpr (!AUG)
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) bacc[bi] += sb[64 * bi + lane];
+            }
+        }
+        if (wave > 0) return;
+        wave_sync();
+    }
     float *lds = smem_f + wave * BigLds<NB>::TOTAL;
     float *bv = lds + BigLds<NB>::BV;
     float *rdst = SEG ? part + (size_t)it.slot * big_slot_elems<NB>() + NBLK * 256 : bv;
@@ -612,22 +654,17 @@ __global__ __launch_bounds__(64 * kBigWPB, big_waves<NB>()) void row_big(
 // Split rows: the partial Gram slots of the row, summed in slot order into
 // the accumulators, then the same factorisation.
 template <int NB>
-__global__ __launch_bounds__(64 * kBigWPB, big_waves<NB>()) void row_finish_big(
-    int K, float alpha, const FinishItem *__restrict__ fin, int64_t n_fin,
+__global__ __launch_bounds__(64, big_waves<NB>()) void row_finish_big(
+    int K, float alpha, const FinishItem *__restrict__ fin,
     const float *__restrict__ part, const floatx4 *__restrict__ img, const float *__restrict__ Lmu,
     float *__restrict__ X, int ldx, uint64_t seed, uint32_t stream,
     const uint32_t *__restrict__ ctr, int *__restrict__ status, int summed)
 {
     constexpr int NBLK = NB * (NB + 1) / 2;
     extern __shared__ float smem_f[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const int64_t fid = (int64_t)blockIdx.x * kBigWPB + wave;
-    if (fid >= n_fin) return;
-    float *lds = smem_f + wave * BigLds<NB>::TOTAL;
-    const int col = lane & 15;
-    const int kq = lane >> 4;
-    const FinishItem f = fin[fid];
+    const int lane = threadIdx.x;
+    float *lds = smem_f;
+    const FinishItem f = fin[blockIdx.x];
     // the row's partial slots summed in slot order (with `summed`, already
     // summed into the first by part_reduce, in the same order)
     const float *src = part + (size_t)f.first * big_slot_elems<NB>();
@@ -676,7 +713,6 @@ __global__ __launch_bounds__(256) void prior_image(int K, const float *__restric
 template <int NB>
 hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
 {
-    const size_t lds = sizeof(float) * kBigWPB * BigLds<NB>::TOTAL;
     const floatx4 *img = (const floatx4 *)sd.Lam_img;
     if (stage == kStagePrior) {
         // the prior image of this sweep (read by the whole rows and the finishing)
@@ -695,9 +731,9 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
             const hipError_t e = launch_part_reduce(c, sd, s, big_slot_elems<NB>());
             if (e != hipSuccess) return e;
         }
-        const unsigned grid = (unsigned)((sd.n_fin + kBigWPB - 1) / kBigWPB);
-        hipLaunchKernelGGL((row_finish_big<NB>), dim3(grid), dim3(64 * kBigWPB), lds, s, c->K,
-                           (float)c->alpha, sd.fin, sd.n_fin, (const float *)c->part, img,
+        hipLaunchKernelGGL((row_finish_big<NB>), dim3((unsigned)sd.n_fin), dim3(64),
+                           sizeof(float) * BigLds<NB>::TOTAL, s, c->K,
+                           (float)c->alpha, sd.fin, (const float *)c->part, img,
                            (const float *)sd.Lmu_w, (float *)sd.X, c->ld, c->seed, sd.stream_row,
                            c->ctr, c->hyp_status + 1, summed ? 1 : 0);
         return hipGetLastError();
@@ -711,29 +747,36 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
     // the rhs from the Gram where the padding has room for the rating
     const int kr = c->K - 16 * (NB - 1);
     const bool aug = kr <= 13 && sd.rc3 != nullptr;
-    auto go = [&](auto kern, int64_t item0, int64_t count, size_t lds_bytes) {
+    auto go = [&](auto kern, int64_t item0, int64_t count, int64_t heavy) {
         if (count <= 0) return;
-        const unsigned grid = (unsigned)((count + kBigWPB - 1) / kBigWPB);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kBigWPB), lds_bytes, s, c->K,
-                           (float)c->alpha, sd.items, item0, item0 + count, sd.nbr,
+        const unsigned grid = (unsigned)(heavy + (count - heavy + kWaves - 1) / kWaves);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), sizeof(float) * BigLds<NB>::GROUP, s, c->K,
+                           (float)c->alpha, sd.items, item0, heavy, item0 + count, sd.nbr,
                            (const float *)sd.rc, (const uint16_t *)sd.rc3, (uint32_t)(c->nnz + 32), ysrc,
                            c->ld, y_bytes, img, (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
                            (float *)c->part, c->seed, sd.stream_row, c->ctr, c->hyp_status + 1);
     };
+    // A wave alone takes about 2 us a chunk at K = 100 whatever else runs, so
+    // unsplit rows of up to 8192 ratings outlasted the rest of their launch:
+    // 17,770 movies with 11.3 M ratings, K = 100, 1640 us -> 980 us with the
+    // rows above the limit dealt; 5775 proteins with 450 k, K = 64, 268 -> 83.
+    const int64_t limit = heavy_limit(sd, c->nnz, c->K, kSimds * big_waves<NB>());
+    const int64_t seg_len = std::max<int64_t>(128, c->split_threshold / 2);
     auto pick = [&](auto segc) {
         constexpr bool SEG = decltype(segc)::value;
         const int64_t item0 = SEG ? 0 : n_seg, count = SEG ? n_seg : n_rows;
-        const size_t bytes = SEG ? 0 : lds;
+        // every segment is heavy if whole ones are
+        const int64_t heavy = SEG ? (seg_len > limit ? count : 0) : whole_rows_above(sd, limit);
         if (bf) {
             if (aug)
-                go(row_big<NB, true, SEG, true>, item0, count, bytes);
+                go(row_big<NB, true, SEG, true>, item0, count, heavy);
             else
-                go(row_big<NB, true, SEG, false>, item0, count, bytes);
+                go(row_big<NB, true, SEG, false>, item0, count, heavy);
         } else {
             if (aug)
-                go(row_big<NB, false, SEG, true>, item0, count, bytes);
+                go(row_big<NB, false, SEG, true>, item0, count, heavy);
             else
-                go(row_big<NB, false, SEG, false>, item0, count, bytes);
+                go(row_big<NB, false, SEG, false>, item0, count, heavy);
         }
     };
     if (stage == kStageSegments)

@@ -92,6 +92,18 @@ __device__ __forceinline__ uint32_t buf_u32_stream(__amdgpu_buffer_rsrc_t r, uin
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, kStreamPolicy);
 }
 
+// Eight consecutive ids from byte offset `off` (any multiple of four).
+__device__ __forceinline__ void buf_ids8(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t (&j)[8])
+{
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kStreamPolicy);
+    const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16u), 0, kStreamPolicy);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        j[e] = a[e];
+        j[4 + e] = b[e];
+    }
+}
+
 __device__ __forceinline__ float buf_f32_stream(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
     return __uint_as_float(buf_u32_stream(r, off));

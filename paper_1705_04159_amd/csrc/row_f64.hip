@@ -335,10 +335,6 @@ __global__ __launch_bounds__(64) void row_finish_f64(int K, double alpha, const 
 // makes a wave walk their ratings one after the other.
 constexpr int64_t kUnpackedItems = 4096;
 
-// Ratings above which a row is heavy (all segments are): 16 to 64 steps of
-// the gather, about as long as the factorisation that follows.
-constexpr int64_t kHeavyRatings = 256;
-
 template <int NB>
 hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
 {
@@ -355,16 +351,8 @@ hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
     }
     if (stage != kStageSegments || sd.n_items == 0) return hipSuccess;
     // the segments come first, then the whole rows in descending degree order
-    int64_t lo = sd.n_split, hi = sd.rows;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        const int32_t r = sd.perm[mid];
-        if (sd.hptr[r + 1] - sd.hptr[r] > kHeavyRatings)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    const int64_t n_heavy = sd.n_slots + lo - sd.n_split, n_light = sd.n_items - n_heavy;
+    const int64_t n_heavy = sd.n_slots + whole_rows_above(sd, heavy_limit(sd, c->nnz, K, 1024 * (NB <= 2 ? 3 : 2)));
+    const int64_t n_light = sd.n_items - n_heavy;
     auto go = [&](auto rpwc) {
         constexpr int RPW = decltype(rpwc)::value;
         const int64_t blocks = n_heavy + (n_light + RPW * kWaves - 1) / (RPW * kWaves);

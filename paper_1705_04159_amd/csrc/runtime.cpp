@@ -563,7 +563,9 @@ int bpmf_create(int64_t M, int64_t N, const int64_t *csr_ptr, const int32_t *csr
             sd.stream_hyp = sid == 0 ? 3u : 4u;
             sd.stream_init = sid == 0 ? 5u : 6u;
             CK(dalloc(&sd.ptr, sd.rows + 1));
-            CK(dalloc(&sd.nbr, nnz));
+            // 32 ids of padding: the row kernels load ids eight at a time
+            CK(dalloc(&sd.nbr, nnz + 32));
+            CK(hipMemset(sd.nbr + nnz, 0, 32 * sizeof(int32_t)));
             CK(hipMalloc(&sd.rc, std::max<size_t>(1, nnz) * es));
             CK(hipMalloc(&sd.X, std::max<size_t>(1, (size_t)sd.rows * c->ld) * es));
             if (c->prec == BPMF_BF16_GRAM) CK(dalloc(&sd.Xbf, (size_t)sd.rows * c->ld));
