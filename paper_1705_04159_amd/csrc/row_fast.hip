@@ -34,6 +34,7 @@
 // Noise: lane c draws normal c of its row (Philox4x32-10 block c/4) with a
 // Box-Muller evaluated in FP32 (the log of u close to 1 is taken as
 // log1p(-(1-u)) so that no bits are lost).
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -69,7 +70,7 @@ __device__ __forceinline__ void gram_item_p3(const RowItem &it, const int32_t *_
                                              floatx4 (&acc)[NB * (NB + 1) / 2], floatx4 (&racc)[NB])
 {
     const uint32_t cnt = (uint32_t)(it.end - it.beg);
-    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, cnt * 4u);
+    const __amdgpu_buffer_rsrc_t jsrc = make_rsrc(nbr + it.beg, (cnt + 32u) * 4u);
     const __amdgpu_buffer_rsrc_t psrc = make_rsrc(rc3 + it.beg, (uint32_t)(3u * plane - (uint32_t)it.beg) * 2u);
     const uint32_t poff = col < 3 ? 2u * ((uint32_t)col * plane + 8u * kq) : kOOB;
     const uint32_t coff = 4u * col;
@@ -79,10 +80,7 @@ __device__ __forceinline__ void gram_item_p3(const RowItem &it, const int32_t *_
     uint32_t jb[8];
     float yv[NB][8];
     u32x4 rp;
-    auto load_ids = [&](uint32_t ch) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) jb[e] = buf_u32_stream(jsrc, (ch * 32 + 8 * kq + e) * 4u);
-    };
+    auto load_ids = [&](uint32_t ch) { buf_ids8(jsrc, (ch * 32 + 8 * kq) * 4u, jb); };
     auto load_rows_t = [&](uint32_t ch, auto checkc) {
         constexpr bool CHECK = decltype(checkc)::value;
 #pragma unroll
@@ -248,14 +246,19 @@ __global__ __launch_bounds__(256) void prior_packed(int K, int KP, const float *
     LamPk[e] = (r < K && cc < K) ? Lam[r * K + cc] : 0.f;
 }
 
+constexpr int kWaves = 4;  // most waves per workgroup of row_fast_f32, and waves of a heavy row
+
 // At least six waves per SIMD asked of the register allocator (K = 32: 71
 // registers, so seven fit), which hides more of the gather latency than
 // the unrestricted allocation's extra unrolling.  With P3 the Gram runs on
 // the BF16 matrix cores from three-part splits of the FP32 rows and the
 // rating planes rc3 (gram_item_p3); otherwise on the FP32 ones.
-template <int NB, int RPW, int WPB, bool P3>
-__global__ __launch_bounds__(64 * WPB, P3 ? 5 : 6) void row_fast_f32(
-    int K, float alpha, const RowItem *__restrict__ items, int64_t item0, int64_t n_items,
+// Workgroups [0, n_heavy) take one heavy item each, a quarter of its ratings
+// to each wave, summed in wave order from the last; the others give each wave
+// RPW consecutive items.
+template <int NB, int RPW, bool P3>
+__global__ __launch_bounds__(64 * kWaves, P3 ? 5 : 6) void row_fast_f32(
+    int K, float alpha, const RowItem *__restrict__ items, int64_t n_heavy, int64_t n_items,
     const int32_t *__restrict__ nbr, const float *__restrict__ rc, const uint16_t *__restrict__ rc3,
     uint32_t plane, const void *__restrict__ Y,
     int ldy, uint32_t y_bytes, const float *__restrict__ LamPk, const float *__restrict__ Lmu,
@@ -269,7 +272,9 @@ __global__ __launch_bounds__(64 * WPB, P3 ? 5 : 6) void row_fast_f32(
     extern __shared__ float smem_f[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const int64_t first = item0 + ((int64_t)blockIdx.x * WPB + wave) * RPW;
+    const bool heavy = (int64_t)blockIdx.x < n_heavy;
+    const int64_t first =
+        heavy ? (int64_t)blockIdx.x : n_heavy + (((int64_t)blockIdx.x - n_heavy) * (blockDim.x >> 6) + wave) * RPW;
     if (first >= n_items) return;
     float *Ps = smem_f + wave * RPW * REGION;
     const int col = lane & 15;
@@ -303,28 +308,54 @@ __global__ __launch_bounds__(64 * WPB, P3 ? 5 : 6) void row_fast_f32(
         constexpr int h = decltype(hc)::value;
         row_of[h] = -1;
         const int64_t id = first + h;
-        if (id >= n_items) return;
+        if (id >= n_items || (h > 0 && heavy)) return;
         const RowItem it = items[id];
+        RowItem mine = it;
+        if (h == 0 && heavy) {  // whole chunks of 32 to each wave
+            const int64_t per = (it.end - it.beg + 32 * kWaves - 1) / (32 * kWaves) * 32;
+            mine.beg = min<int64_t>(it.end, it.beg + wave * per);
+            mine.end = min<int64_t>(it.end, mine.beg + per);
+        }
         floatx4 acc[NBLK];
 #pragma unroll
         for (int q = 0; q < NBLK; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
         float bacc[NB];
         if constexpr (P3) {
             floatx4 racc[NB];
-            gram_item_p3<NB>(it, nbr, rc3, plane, ysrc, ldy4, kq, col, acc, racc);
+            gram_item_p3<NB>(mine, nbr, rc3, plane, ysrc, ldy4, kq, col, acc, racc);
             // rows 0..2 of the rhs tile (lanes 0..15: kq = 0), the three rating parts
 #pragma unroll
             for (int bi = 0; bi < NB; ++bi) bacc[bi] = (racc[bi][0] + racc[bi][1]) + racc[bi][2];
         } else {
 #pragma unroll
             for (int bi = 0; bi < NB; ++bi) bacc[bi] = 0.f;
-            gram_item<NB, true>(it, nbr, rc, ysrc, ldy4, lane_off, kq, acc, bacc);
+            gram_item<NB, true>(mine, nbr, rc, ysrc, ldy4, lane_off, kq, acc, bacc);
             // sum the rhs over the four rating slots of each 16-lane column
 #pragma unroll
             for (int bi = 0; bi < NB; ++bi) {
                 bacc[bi] += __shfl_xor(bacc[bi], 16);
                 bacc[bi] += __shfl_xor(bacc[bi], 32);
             }
+        }
+        if (h == 0 && heavy) {
+            floatx4 *sa = reinterpret_cast<floatx4 *>(smem_f + kWaves * RPW * REGION);
+            float *sb = smem_f + kWaves * RPW * REGION + NBLK * 256;
+            for (int w = kWaves - 1; w > 0; --w) {
+                if (wave == w) {
+#pragma unroll
+                    for (int q = 0; q < NBLK; ++q) sa[64 * q + lane] = acc[q];
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) sb[64 * bi + lane] = bacc[bi];
+                }
+                __syncthreads();
+                if (wave == w - 1) {
+#pragma unroll
+                    for (int q = 0; q < NBLK; ++q) acc[q] += sa[64 * q + lane];
+#pragma unroll
+                    for (int bi = 0; bi < NB; ++bi) bacc[bi] += sb[64 * bi + lane];
+                }
+            }
+            if (wave > 0) return;
         }
         if (it.slot >= 0) {  // segment of a split row: raw partial sums
             float *dst = part + (size_t)it.slot * (KK2 + K);
@@ -366,6 +397,7 @@ __global__ __launch_bounds__(64 * WPB, P3 ? 5 : 6) void row_fast_f32(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
+    if (heavy && wave > 0) return;
     // column-per-lane within each lane group; groups without a full row
     // factor the identity and write nothing
     const int grp = lane / LPR;
@@ -551,20 +583,34 @@ hipError_t launch_finish_f32(bpmf_ctx *c, Side &sd, hipStream_t s)
     return hipGetLastError();
 }
 
-// Work items [item0, item_end): the segments of split rows are [0, n_slots),
-// the whole rows follow, the rank-one path takes the last n_low.
-template <int NB, int RPW, int WPB>
-hipError_t launch_f32(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int64_t item0, int64_t item_end)
+// The work items before the rank-one path's: the segments of split rows, then
+// the whole rows.  The segments and the heavy rows start first and the light
+// rows fill in behind them, which balances the load better than two launches
+// (measured); the rank-one path (whole rows stage) still runs beside it.
+template <int NB, int RPW>
+hipError_t launch_f32(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s)
 {
     constexpr int KP = 16 * NB;
-    const size_t lds = sizeof(float) * WPB * RPW * (KP * (KP + 1) / 2 + KP);
-    const int64_t count = item_end - item0;
-    const int64_t per_block = (int64_t)WPB * RPW;
-    const unsigned grid = (unsigned)((count + per_block - 1) / per_block);
+    constexpr int NBLK = NB * (NB + 1) / 2;
+    const int64_t count = sd.n_items - sd.n_low;
     if (count <= 0) return hipSuccess;
-    auto go = [&](auto kern, const void *Y, uint32_t y_bytes) {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WPB), lds, s, c->K, (float)c->alpha, sd.items, item0,
-                           item_end, sd.nbr, (const float *)sd.rc, (const uint16_t *)sd.rc3,
+    auto go = [&](auto kern, int64_t waves, const void *Y, uint32_t y_bytes) {
+        // rows above the limit go to four waves: 20,000 users with 1.8 M
+        // ratings, K = 16, four rows of up to 2048 ratings a wave otherwise:
+        // 157 -> 53 us.  At K = 32 the one-wave workgroups that heavy rows
+        // exclude are worth more than the last of the tail, so a row must
+        // take the whole stage rather than half of it (50,000 users with
+        // 5.4 M ratings: 187 us with the limit at half, 182 with none heavy)
+        const int64_t limit = heavy_limit(sd, c->nnz, c->K, (NB == 1 ? 1024 : 512) * waves);
+        const int64_t seg_len = std::max<int64_t>(128, c->split_threshold / 2);
+        const int64_t n_heavy = seg_len > limit ? sd.n_slots + whole_rows_above(sd, limit) : 0;
+        // workgroups as small as the heavy rows allow: at K = 32 one-wave ones
+        // are the fastest (20M shape, four waves: movies 307 -> 334 us)
+        const int wpb = n_heavy || NB == 1 ? kWaves : (NB == 2 ? 1 : 2);
+        const size_t lds = sizeof(float) * (wpb * RPW * (KP * (KP + 1) / 2 + KP) + (n_heavy ? 64 * (4 * NBLK + NB) : 0));
+        const unsigned grid = (unsigned)(n_heavy + (count - n_heavy + wpb * RPW - 1) / (wpb * RPW));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * wpb), lds, s, c->K, (float)c->alpha, sd.items, n_heavy,
+                           count, sd.nbr, (const float *)sd.rc, (const uint16_t *)sd.rc3,
                            (uint32_t)(c->nnz + 32), Y, c->ld, y_bytes, (const float *)sd.Lam_pk,
                            (const float *)sd.Lmu_w, (float *)sd.X, c->ld, (float *)c->part, c->seed,
                            sd.stream_row, c->ctr, c->hyp_status + 1);
@@ -572,11 +618,11 @@ hipError_t launch_f32(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int64_t it
     const uint32_t y_bytes = (uint32_t)(ot.rows * c->ld * sizeof(float));
     if constexpr (NB <= 2) {
         if (sd.rc3) {
-            go(row_fast_f32<NB, RPW, WPB, true>, ot.X, y_bytes);
+            go(row_fast_f32<NB, RPW, true>, 5, ot.X, y_bytes);
             return hipGetLastError();
         }
     }
-    go(row_fast_f32<NB, RPW, WPB, false>, ot.X, y_bytes);
+    go(row_fast_f32<NB, RPW, false>, NB <= 2 ? 6 : 3, ot.X, y_bytes);
     return hipGetLastError();
 }
 
@@ -669,19 +715,13 @@ hipError_t launch_row_fast(bpmf_ctx *c, int side_id, hipStream_t s, int stage, b
         case 3: return launch_finish_f32<3, 2>(c, sd, s);
         default: return launch_finish_f32<4, 2>(c, sd, s);
         }
-    case kStageSegments: {
-        // segments and whole rows in one launch: the heavy segments start
-        // first and the whole rows fill in behind them, which balances the
-        // load better than two launches (measured); the rank-one path (whole
-        // rows stage) still runs beside it
-        const int64_t e = sd.n_items - sd.n_low;
+    case kStageSegments:
         switch (nb) {
-        case 1: return launch_f32<1, 4, 4>(c, sd, ot, s, 0, e);
-        case 2: return launch_f32<2, 2, 1>(c, sd, ot, s, 0, e);  // one-wave blocks: measured best
-        case 3: return launch_f32<3, 1, 2>(c, sd, ot, s, 0, e);
-        default: return launch_f32<4, 1, 2>(c, sd, ot, s, 0, e);
+        case 1: return launch_f32<1, 4>(c, sd, ot, s);
+        case 2: return launch_f32<2, 2>(c, sd, ot, s);
+        case 3: return launch_f32<3, 1>(c, sd, ot, s);
+        default: return launch_f32<4, 1>(c, sd, ot, s);
         }
-    }
     default: return hipSuccess;
     }
 }
