@@ -266,14 +266,14 @@ constexpr int kRedThreads = 512;
 __global__ __launch_bounds__(kRedThreads) void hyper_reduce(int K, int nblk, const double *__restrict__ part,
                                                             double *__restrict__ stats, int entry_groups,
                                                             double nu_s, uint64_t seed, uint32_t stream,
-                                                            const uint32_t *__restrict__ ctr, uint32_t t_off,
+                                                            SweepT sweep,
                                                             double *__restrict__ noise, int *__restrict__ status)
 {
     __shared__ double ws[kRedThreads / 64][16];
     const int tid = threadIdx.x;
     const int E = K + K * (K + 1) / 2;
     if ((int)blockIdx.x >= entry_groups) {
-        const uint32_t t = ctr[0] + t_off;
+        const uint32_t t = sweep.t();
         const int n_low = K * (K - 1) / 2, b_low = (n_low + 3) / 4, b_mu = (K + 3) / 4;
         const int job = ((int)blockIdx.x - entry_groups) * kRedThreads + tid;
         if (job < b_low + b_mu) {
@@ -816,7 +816,7 @@ hipError_t launch_hyper(bpmf_ctx *c, int side_id, hipStream_t s, uint32_t t_off)
     const int jobs = (K * (K - 1) / 2 + 3) / 4 + (K + 3) / 4 + K;
     hipLaunchKernelGGL(hyper_reduce, dim3(groups + (jobs + kRedThreads - 1) / kRedThreads), dim3(kRedThreads), 0, s,
                        K, used, (const double *)part, stats, groups, c->nu0 + (double)rows, c->seed, sd.stream_hyp,
-                       c->ctr, t_off, noise, c->hyp_status);
+                       c->sweep_t(t_off), noise, c->hyp_status);
     const size_t lds = draw_lds(K);
     // K <= 64: four waves (at most four block columns), which find room beside
     // the other side's row kernels; above, eight

@@ -38,6 +38,15 @@ struct FoldItem {
     int64_t end;
 };
 
+// The sweep index of a launch: read from the device counter (sweeps of the
+// captured graph), or known to the host (single calls), which spares those a
+// launch that only sets the counter.
+struct SweepT {
+    const uint32_t *ctr;
+    uint32_t off;
+    __device__ __forceinline__ uint32_t t() const { return (ctr ? ctr[0] : 0u) + off; }
+};
+
 struct FoldinState;  // fold-in server (foldin.cpp)
 
 // Stages of one side's row update (the item loop of Algorithm 1), in an
@@ -124,11 +133,18 @@ struct bpmf_ctx {
     // memory that kernels clear in place, so that reading them after a
     // call's one synchronisation costs no copy
     int *hyp_status = nullptr;
+    double *h_rmse = nullptr;  // [2] beside them: the RMSEs of a single prediction call
     // split partials
     void *part = nullptr;
     int64_t part_slots = 0;
     // device counters: [0] = t, [1] = t0 of the running graph, [2] = running-mean count
     uint32_t *ctr = nullptr;
+    bool t_known = false;                    // while a single call queues its work: t_now is its sweep index
+    uint32_t t_now = 0;
+    bpmf::SweepT sweep_t(uint32_t off = 0) const
+    {
+        return t_known ? bpmf::SweepT{nullptr, t_now + off} : bpmf::SweepT{ctr, off};
+    }
     // staging of host factor copies: two chunks each on the device and in pinned
     // host memory
     void *io_dev = nullptr, *io_pin = nullptr;
@@ -205,10 +221,15 @@ hipError_t launch_row_update(bpmf_ctx *c, int side_id, hipStream_t s);
 // Hyper draw of one side (statistics, reduction, single-workgroup draw) for
 // sweep ctr[0] + t_off.
 hipError_t launch_hyper(bpmf_ctx *c, int side_id, hipStream_t s, uint32_t t_off = 0);
-// Predict the registered test set as sweep ctr[0]; writes rmse_hist[slot].
+// Predict the registered test set as sweep c->sweep_t(); writes rmse_hist[slot],
+// or h_rmse in a single call.
 hipError_t launch_predict_test(bpmf_ctx *c, hipStream_t s);
 hipError_t launch_predict_pairs(bpmf_ctx *c, int64_t n, const int32_t *row, const int32_t *col,
                                 float *out, hipStream_t s);
+// The same for caller ids (mapped by a relabelled context) in memory that the
+// device reads in place.
+hipError_t launch_predict_pairs_mapped(bpmf_ctx *c, int64_t n, const int32_t *row, const int32_t *col, float *out,
+                                       hipStream_t s);
 // Caller ids to internal rows in place (relabelled contexts): row[e] and col[e]
 // through d_int_of of the user and movie sides.
 hipError_t launch_map_pairs(bpmf_ctx *c, int64_t n, int32_t *row, int32_t *col, hipStream_t s);

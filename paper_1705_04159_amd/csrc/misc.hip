@@ -67,13 +67,13 @@ template <typename T, int G>
 __global__ __launch_bounds__(256) void predict_test(
     int K, int ld, int64_t n, const int32_t *__restrict__ row, const int32_t *__restrict__ col,
     const float *__restrict__ val, const T *__restrict__ U, const T *__restrict__ V, double rbar,
-    double *__restrict__ pred_sum, const uint32_t *__restrict__ ctr, int burn_in,
+    double *__restrict__ pred_sum, SweepT sweep, const uint32_t *__restrict__ ctr, int burn_in,
     double *__restrict__ part)
 {
     constexpr int GPB = 256 / G;  // groups per block
     constexpr int P = 4;          // pairs per group in flight
     __shared__ double red[2][GPB];
-    const uint32_t t = ctr[0];
+    const uint32_t t = sweep.t();
     const uint32_t cnt = ctr[2];
     const bool use = (int64_t)t > (int64_t)burn_in;
     const int g = threadIdx.x % G;
@@ -146,10 +146,10 @@ __global__ __launch_bounds__(256) void predict_test(
 
 // One block: sum the per-block partials (each thread a fixed strided subset,
 // then a fixed tree), store the RMSEs of this sweep in hist[slot],
-// slot = t - t0, and count the sweep into the running mean if t > burn_in.
+// slot = t - t0 (0 in a single call), and count the sweep into the running mean if t > burn_in.
 __global__ __launch_bounds__(256) void predict_finalize(int nblk, int64_t n,
                                                         const double *__restrict__ part,
-                                                        uint32_t *__restrict__ ctr, int burn_in,
+                                                        SweepT sweep, uint32_t *__restrict__ ctr, int burn_in,
                                                         double *__restrict__ hist, int64_t hist_cap)
 {
     __shared__ double red[2][256];
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256) void predict_finalize(int nblk, int64_t n,
         __syncthreads();
     }
     if (tid != 0) return;
-    const uint32_t t = ctr[0];
-    int64_t slot = (int64_t)t - (int64_t)ctr[1];
+    const uint32_t t = sweep.t();
+    int64_t slot = sweep.ctr ? (int64_t)t - (int64_t)ctr[1] : 0;  // a single call has one entry
     if (slot < 0 || slot >= hist_cap) slot = hist_cap - 1;
     const double dn = n > 0 ? (double)n : 1.0;
     hist[2 * slot] = sqrt(red[0][0] / dn);
@@ -190,6 +190,39 @@ __global__ void predict_pairs(int K, int ld, int64_t n, const int32_t *__restric
     if (e >= n) return;
     double p = group_dot<T>(K, U + (size_t)row[e] * ld, V + (size_t)col[e] * ld, g) + rbar;
     if (g == 0) out[e] = (float)p;
+}
+
+// predict_pairs for ids and predictions in host memory and caller ids: a wave
+// moves 64 pairs' ids and results in whole 256-byte accesses (each crosses
+// PCIe once), maps the ids where the context is relabelled, and takes the
+// pairs four at a time, 16 lanes each, as predict_pairs does.
+template <typename T>
+__global__ __launch_bounds__(256) void predict_pairs_mapped(int K, int ld, int64_t n, const int32_t *__restrict__ row,
+                                                            const int32_t *__restrict__ col,
+                                                            const int32_t *__restrict__ urow,
+                                                            const int32_t *__restrict__ vrow,
+                                                            const T *__restrict__ U, const T *__restrict__ V,
+                                                            double rbar, float *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+    if (base >= n) return;
+    const int64_t e = base + lane;
+    int32_t r = e < n ? row[e] : 0, c = e < n ? col[e] : 0;
+    if (urow) {
+        r = urow[r];
+        c = vrow[c];
+    }
+    float mine = 0.f;
+#pragma unroll 4
+    for (int it = 0; it < 16; ++it) {
+        const int src = 4 * it + (lane >> 4);
+        const int32_t rr = __shfl(r, src), cc = __shfl(c, src);  // pairs past n: row 0, not written
+        const float p = (float)(group_dot<T>(K, U + (size_t)rr * ld, V + (size_t)cc * ld, lane & 15) + rbar);
+        const float q = __shfl(p, (lane & 3) << 4);
+        if (it == (lane >> 2)) mine = q;
+    }
+    if (e < n) out[e] = mine;
 }
 
 __global__ void set_counter(uint32_t *ctr, int idx, uint32_t v) { ctr[idx] = v; }
@@ -268,19 +301,20 @@ hipError_t launch_predict_test(bpmf_ctx *c, hipStream_t s)
         hipLaunchKernelGGL((predict_test<double, 16>), dim3(nblk), dim3(256), 0, s, c->K, c->ld,
                            c->n_test, c->test_row, c->test_col, c->test_val,
                            (const double *)c->side[0].X, (const double *)c->side[1].X, c->rbar,
-                           c->pred_sum, c->ctr, c->burn_in, c->rmse_part);
+                           c->pred_sum, c->sweep_t(), c->ctr, c->burn_in, c->rmse_part);
     else if (c->ld <= 32)  // four lanes per pair: twice the pairs in flight per wavefront
         hipLaunchKernelGGL((predict_test<float, 4>), dim3(nblk), dim3(256), 0, s, c->K, c->ld,
                            c->n_test, c->test_row, c->test_col, c->test_val,
                            (const float *)c->side[0].X, (const float *)c->side[1].X, c->rbar,
-                           c->pred_sum, c->ctr, c->burn_in, c->rmse_part);
+                           c->pred_sum, c->sweep_t(), c->ctr, c->burn_in, c->rmse_part);
     else  // eight lanes per pair, several float4 steps each
         hipLaunchKernelGGL((predict_test<float, 8>), dim3(nblk), dim3(256), 0, s, c->K, c->ld,
                            c->n_test, c->test_row, c->test_col, c->test_val,
                            (const float *)c->side[0].X, (const float *)c->side[1].X, c->rbar,
-                           c->pred_sum, c->ctr, c->burn_in, c->rmse_part);
+                           c->pred_sum, c->sweep_t(), c->ctr, c->burn_in, c->rmse_part);
     hipLaunchKernelGGL(predict_finalize, dim3(1), dim3(256), 0, s, nblk, c->n_test, c->rmse_part,
-                       c->ctr, c->burn_in, c->rmse_hist, c->hist_cap);
+                       c->sweep_t(), c->ctr, c->burn_in, c->t_known ? c->h_rmse : c->rmse_hist,
+                       c->t_known ? 1 : c->hist_cap);
     return hipGetLastError();
 }
 
@@ -297,6 +331,22 @@ hipError_t launch_predict_pairs(bpmf_ctx *c, int64_t n, const int32_t *row, cons
         hipLaunchKernelGGL((predict_pairs<float>), dim3(grid), dim3(256), 0, s, c->K, c->ld, n,
                            row, col, (const float *)c->side[0].X, (const float *)c->side[1].X,
                            c->rbar, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_predict_pairs_mapped(bpmf_ctx *c, int64_t n, const int32_t *row, const int32_t *col, float *out,
+                                       hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    const unsigned grid = (unsigned)((n + 255) / 256);
+    auto go = [&](auto kern, auto *U, auto *V) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, c->K, c->ld, n, row, col,
+                           (const int32_t *)c->d_int_of[0], (const int32_t *)c->d_int_of[1], U, V, c->rbar, out);
+    };
+    if (c->prec == 0)
+        go(predict_pairs_mapped<double>, (const double *)c->side[0].X, (const double *)c->side[1].X);
+    else
+        go(predict_pairs_mapped<float>, (const float *)c->side[0].X, (const float *)c->side[1].X);
     return hipGetLastError();
 }
 

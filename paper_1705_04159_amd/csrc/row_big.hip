@@ -562,7 +562,7 @@ __global__ __launch_bounds__(64 * kWaves, big_waves<NB>()) void row_big(
     const int32_t *__restrict__ nbr, const float *__restrict__ rc, const uint16_t *__restrict__ rc3,
     uint32_t plane, const void *__restrict__ Y, int ldy, uint32_t y_bytes, const floatx4 *__restrict__ img,
     const float *__restrict__ Lmu, float *__restrict__ X, int ldx, float *__restrict__ part, uint64_t seed,
-    uint32_t stream, const uint32_t *__restrict__ ctr, int *__restrict__ status)
+    uint32_t stream, SweepT sweep, int *__restrict__ status)
 {
     constexpr int NBLK = NB * (NB + 1) / 2;
     extern __shared__ float smem_f[];
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(64 * kWaves, big_waves<NB>()) void row_big(
                 bv[c] = c < K ? alpha * bv[c] + Lmu[c] : 0.f;
             }
         wave_sync();
-        blocked_chol_sample<NB>(acc, lds, K, alpha, img, (uint32_t)it.row, ctr[0], seed, stream,
+        blocked_chol_sample<NB>(acc, lds, K, alpha, img, (uint32_t)it.row, sweep.t(), seed, stream,
                                 X + (size_t)it.row * ldx, status);
     }
 }
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(64, big_waves<NB>()) void row_finish_big(
     int K, float alpha, const FinishItem *__restrict__ fin,
     const float *__restrict__ part, const floatx4 *__restrict__ img, const float *__restrict__ Lmu,
     float *__restrict__ X, int ldx, uint64_t seed, uint32_t stream,
-    const uint32_t *__restrict__ ctr, int *__restrict__ status, int summed)
+    SweepT sweep, int *__restrict__ status, int summed)
 {
     constexpr int NBLK = NB * (NB + 1) / 2;
     extern __shared__ float smem_f[];
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(64, big_waves<NB>()) void row_finish_big(
         if (c < 16 * NB) bv[c] = c < K ? alpha * bs[h] + Lmu[c] : 0.f;
     }
     wave_sync();
-    blocked_chol_sample<NB>(acc, lds, K, alpha, img, (uint32_t)f.row, ctr[0], seed, stream,
+    blocked_chol_sample<NB>(acc, lds, K, alpha, img, (uint32_t)f.row, sweep.t(), seed, stream,
                             X + (size_t)f.row * ldx, status);
 }
 
@@ -735,7 +735,7 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
                            sizeof(float) * BigLds<NB>::TOTAL, s, c->K,
                            (float)c->alpha, sd.fin, (const float *)c->part, img,
                            (const float *)sd.Lmu_w, (float *)sd.X, c->ld, c->seed, sd.stream_row,
-                           c->ctr, c->hyp_status + 1, summed ? 1 : 0);
+                           c->sweep_t(), c->hyp_status + 1, summed ? 1 : 0);
         return hipGetLastError();
     }
     if (stage != kStageSegments && stage != kStageRows) return hipSuccess;
@@ -754,7 +754,7 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
                            (float)c->alpha, sd.items, item0, heavy, item0 + count, sd.nbr,
                            (const float *)sd.rc, (const uint16_t *)sd.rc3, (uint32_t)(c->nnz + 32), ysrc,
                            c->ld, y_bytes, img, (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
-                           (float *)c->part, c->seed, sd.stream_row, c->ctr, c->hyp_status + 1);
+                           (float *)c->part, c->seed, sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     };
     // A wave alone takes about 2 us a chunk at K = 100 whatever else runs, so
     // unsplit rows of up to 8192 ratings outlasted the rest of their launch:

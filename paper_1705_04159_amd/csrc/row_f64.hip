@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * kWaves) void row_f64(
     int K, double alpha, const RowItem *__restrict__ items, int64_t n_heavy, int64_t n_items,
     const int32_t *__restrict__ nbr, const double *__restrict__ rc, const double *__restrict__ Y,
     uint32_t y_bytes, const double *__restrict__ Lam, const double *__restrict__ Lmu, double *__restrict__ X,
-    double *__restrict__ part, uint64_t seed, uint32_t stream, const uint32_t *__restrict__ ctr,
+    double *__restrict__ part, uint64_t seed, uint32_t stream, SweepT sweep,
     int *__restrict__ status)
 {
     constexpr int KP = 16 * NB;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(64 * kWaves) void row_f64(
     for (int r = 0; r < KP; ++r)
         v[r] = (live && r < K) ? Lam[r * K + c] + alpha * P[r >= cc ? pk(r, cc) : pk(cc, r)] : (r == c ? 1.0 : 0.0);
     v[KP] = live ? Lmu[c] + alpha * P[PE + cc] : 0.0;
-    const double x = chol_sample_f64<KP, RPW>(v, K, c, (uint32_t)my_row, ctr[0], seed, stream, live, status);
+    const double x = chol_sample_f64<KP, RPW>(v, K, c, (uint32_t)my_row, sweep.t(), seed, stream, live, status);
     if (live) X[(size_t)my_row * K + c] = x;
 }
 
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(64) void row_finish_f64(int K, double alpha, const 
                                                      const double *__restrict__ Lam,
                                                      const double *__restrict__ Lmu, double *__restrict__ X,
                                                      uint64_t seed, uint32_t stream,
-                                                     const uint32_t *__restrict__ ctr, int *__restrict__ status)
+                                                     SweepT sweep, int *__restrict__ status)
 {
     constexpr int KP = 16 * NB;
     const int c = threadIdx.x;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(64) void row_finish_f64(int K, double alpha, const 
     for (int r = 0; r < KP; ++r)
         v[r] = (live && r < K) ? Lam[r * K + c] + alpha * src[r >= c ? pk(r, c) : pk(c, r)] : (r == c ? 1.0 : 0.0);
     v[KP] = live ? Lmu[c] + alpha * src[KK2 + c] : 0.0;
-    const double x = chol_sample_f64<KP, 1>(v, K, c, (uint32_t)f.row, ctr[0], seed, stream, live, status);
+    const double x = chol_sample_f64<KP, 1>(v, K, c, (uint32_t)f.row, sweep.t(), seed, stream, live, status);
     if (live) X[(size_t)f.row * K + c] = x;
 }
 
@@ -346,7 +346,7 @@ hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
                            sd.fin, E, (double *)c->part);
         hipLaunchKernelGGL((row_finish_f64<NB>), dim3((unsigned)sd.n_fin), dim3(64), 0, s, K, c->alpha, sd.fin,
                            (const double *)c->part, (const double *)sd.Lam_w, (const double *)sd.Lmu_w,
-                           (double *)sd.X, c->seed, sd.stream_row, c->ctr, c->hyp_status + 1);
+                           (double *)sd.X, c->seed, sd.stream_row, c->sweep_t(), c->hyp_status + 1);
         return hipGetLastError();
     }
     if (stage != kStageSegments || sd.n_items == 0) return hipSuccess;
@@ -360,7 +360,7 @@ hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
                            sd.items, n_heavy, sd.n_items, sd.nbr, (const double *)sd.rc, (const double *)ot.X,
                            (uint32_t)(ot.rows * K * sizeof(double)), (const double *)sd.Lam_w,
                            (const double *)sd.Lmu_w, (double *)sd.X, (double *)c->part, c->seed, sd.stream_row,
-                           c->ctr, c->hyp_status + 1);
+                           c->sweep_t(), c->hyp_status + 1);
     };
     constexpr int kPacked = NB == 1 ? 4 : (NB == 2 ? 2 : 1);
     if (n_light > kUnpackedItems)

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(64 * kWaves, P3 ? 5 : 6) void row_fast_f32(
     uint32_t plane, const void *__restrict__ Y,
     int ldy, uint32_t y_bytes, const float *__restrict__ LamPk, const float *__restrict__ Lmu,
     float *__restrict__ X, int ldx, float *__restrict__ part, uint64_t seed, uint32_t stream,
-    const uint32_t *__restrict__ ctr, int *__restrict__ status)
+    SweepT sweep, int *__restrict__ status)
 {
     constexpr int KP = 16 * NB;
     constexpr int NBLK = NB * (NB + 1) / 2;
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * kWaves, P3 ? 5 : 6) void row_fast_f32(
 #pragma unroll
     for (int r = 0; r < KP; ++r) v[r] = (live && r < K) ? P[r >= cc ? pk(r, cc) : pk(cc, r)] : (r == c ? 1.f : 0.f);
     v[KP] = live ? alpha * P[KP * (KP + 1) / 2 + cc] + Lmu[c] : 0.f;
-    const float x = chol_sample_column<KP, RPW>(v, K, c, (uint32_t)my_row, ctr[0], 0u, seed, stream,
+    const float x = chol_sample_column<KP, RPW>(v, K, c, (uint32_t)my_row, sweep.t(), 0u, seed, stream,
                                                 live, status);
     if (live) X[(size_t)my_row * ldx + c] = x;
 }
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(64 * WPB) void row_finish_fast(
     int K, float alpha, const FinishItem *__restrict__ fin, int64_t n_fin,
     const float *__restrict__ part, const float *__restrict__ Lam, const float *__restrict__ Lmu,
     float *__restrict__ X, int ldx, uint64_t seed, uint32_t stream,
-    const uint32_t *__restrict__ ctr, int *__restrict__ status)
+    SweepT sweep, int *__restrict__ status)
 {
     constexpr int KP = 16 * NB;
     const int c = threadIdx.x & 63;
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * WPB) void row_finish_fast(
         v[r] = (live && r < K) ? alpha * src[r >= c ? pk(r, c) : pk(c, r)] + Lam[r * K + c]
                                : (r == c ? 1.f : 0.f);
     v[KP] = live ? alpha * src[KK2 + c] + Lmu[c] : 0.f;
-    const float x = chol_sample_column<KP, 1>(v, K, c, (uint32_t)f.row, ctr[0], 0u, seed, stream,
+    const float x = chol_sample_column<KP, 1>(v, K, c, (uint32_t)f.row, sweep.t(), 0u, seed, stream,
                                               live, status);
     if (live) X[(size_t)f.row * ldx + c] = x;
 }
@@ -579,7 +579,7 @@ hipError_t launch_finish_f32(bpmf_ctx *c, Side &sd, hipStream_t s)
     hipLaunchKernelGGL((row_finish_fast<NB, WPB>), dim3(grid), dim3(64 * WPB), 0, s, c->K,
                        (float)c->alpha, sd.fin, sd.n_fin, (const float *)c->part,
                        (const float *)sd.Lam_w, (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
-                       c->seed, sd.stream_row, c->ctr, c->hyp_status + 1);
+                       c->seed, sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     return hipGetLastError();
 }
 
@@ -613,7 +613,7 @@ hipError_t launch_f32(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s)
                            count, sd.nbr, (const float *)sd.rc, (const uint16_t *)sd.rc3,
                            (uint32_t)(c->nnz + 32), Y, c->ld, y_bytes, (const float *)sd.Lam_pk,
                            (const float *)sd.Lmu_w, (float *)sd.X, c->ld, (float *)c->part, c->seed,
-                           sd.stream_row, c->ctr, c->hyp_status + 1);
+                           sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     };
     const uint32_t y_bytes = (uint32_t)(ot.rows * c->ld * sizeof(float));
     if constexpr (NB <= 2) {

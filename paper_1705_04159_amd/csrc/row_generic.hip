@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void row_update_generic(
     int K, T alpha, const RowItem *__restrict__ items, const int32_t *__restrict__ nbr,
     const T *__restrict__ rc, const YT *__restrict__ Y, int ldy, const T *__restrict__ Lam,
     const T *__restrict__ Lmu, T *__restrict__ X, int ldx, T *__restrict__ part, uint64_t seed,
-    uint32_t stream, const uint32_t *__restrict__ ctr, int *__restrict__ status)
+    uint32_t stream, SweepT sweep, int *__restrict__ status)
 {
     extern __shared__ __align__(16) char smem_raw[];
     Smem<T> s = carve<T>(smem_raw, K);
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void row_update_generic(
     }
     if (tid < K) s.b[tid] = Lmu[tid] + alpha * bacc;
     __syncthreads();
-    factor_and_sample<T>(K, s, seed, stream, ctr[0], (uint32_t)it.row, status);
+    factor_and_sample<T>(K, s, seed, stream, sweep.t(), (uint32_t)it.row, status);
     if (tid < K) X[(size_t)it.row * ldx + tid] = s.b[tid];
 }
 
@@ -191,7 +191,7 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void row_finish_generic(
     int K, T alpha, const FinishItem *__restrict__ fin, const T *__restrict__ part,
     const T *__restrict__ Lam, const T *__restrict__ Lmu, T *__restrict__ X, int ldx,
-    uint64_t seed, uint32_t stream, const uint32_t *__restrict__ ctr, int *__restrict__ status)
+    uint64_t seed, uint32_t stream, SweepT sweep, int *__restrict__ status)
 {
     extern __shared__ __align__(16) char smem_raw[];
     Smem<T> s = carve<T>(smem_raw, K);
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void row_finish_generic(
         }
     }
     __syncthreads();
-    factor_and_sample<T>(K, s, seed, stream, ctr[0], (uint32_t)f.row, status);
+    factor_and_sample<T>(K, s, seed, stream, sweep.t(), (uint32_t)f.row, status);
     if (tid < K) X[(size_t)f.row * ldx + tid] = s.b[tid];
 }
 
@@ -246,13 +246,13 @@ hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage
                                (const double *)sd.rc, (const double *)ot.X, c->ld,
                                (const double *)sd.Lam_w, (const double *)sd.Lmu_w,
                                (double *)sd.X, c->ld, (double *)c->part, c->seed, sd.stream_row,
-                               c->ctr, c->hyp_status + 1);
+                               c->sweep_t(), c->hyp_status + 1);
         if (stage == kStageFinish && sd.n_fin > 0)
             hipLaunchKernelGGL((row_finish_generic<double>), dim3((unsigned)sd.n_fin),
                                dim3(kThreads), lds, s, K, c->alpha, sd.fin,
                                (const double *)c->part, (const double *)sd.Lam_w,
                                (const double *)sd.Lmu_w, (double *)sd.X, c->ld, c->seed,
-                               sd.stream_row, c->ctr, c->hyp_status + 1);
+                               sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     } else {
         size_t lds = lds_bytes<float>(K);
         if (stage == kStageSegments && sd.n_items > 0) {
@@ -262,7 +262,7 @@ hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage
                                    (float)c->alpha, sd.items, sd.nbr, (const float *)sd.rc,
                                    (const uint16_t *)ot.Xbf, c->ld, (const float *)sd.Lam_w,
                                    (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
-                                   (float *)c->part, c->seed, sd.stream_row, c->ctr,
+                                   (float *)c->part, c->seed, sd.stream_row, c->sweep_t(),
                                    c->hyp_status + 1);
             else
                 hipLaunchKernelGGL((row_update_generic<float, float>), dim3((unsigned)sd.n_items),
@@ -270,14 +270,14 @@ hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage
                                    (const float *)sd.rc, (const float *)ot.X, c->ld,
                                    (const float *)sd.Lam_w, (const float *)sd.Lmu_w,
                                    (float *)sd.X, c->ld, (float *)c->part, c->seed,
-                                   sd.stream_row, c->ctr, c->hyp_status + 1);
+                                   sd.stream_row, c->sweep_t(), c->hyp_status + 1);
         }
         if (stage == kStageFinish && sd.n_fin > 0)
             hipLaunchKernelGGL((row_finish_generic<float>), dim3((unsigned)sd.n_fin),
                                dim3(kThreads), lds, s, K, (float)c->alpha, sd.fin,
                                (const float *)c->part, (const float *)sd.Lam_w,
                                (const float *)sd.Lmu_w, (float *)sd.X, c->ld, c->seed,
-                               sd.stream_row, c->ctr, c->hyp_status + 1);
+                               sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     }
     return hipGetLastError();
 }

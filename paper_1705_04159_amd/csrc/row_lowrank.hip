@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64 * kLowWPB) void row_lowrank(
     int K, float alpha, const RowItem *__restrict__ items, int64_t item0, int64_t n_items,
     const int32_t *__restrict__ nbr, const float *__restrict__ rc, const float *__restrict__ Yt,
     int ld, const float *__restrict__ Linv, const float *__restrict__ Ltmu, float *__restrict__ X,
-    int ldx, uint64_t seed, uint32_t stream, const uint32_t *__restrict__ ctr)
+    int ldx, uint64_t seed, uint32_t stream, SweepT sweep)
 {
     constexpr int KP = 16 * C;
     __shared__ float Ms[KP * KP];  // Ms[m][c] = L_Lam^-1[m][c] (lower), padding 0
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(64 * kLowWPB) void row_lowrank(
     if constexpr (C == 4) {
         // components 4 l16 .. 4 l16 + 3: the four normals of Philox block l16
         if (4 * l16 < K) {
-            const Block4 bl = philox4x32_10(row, ctr[0], (stream << 24) | (uint32_t)l16, 0u, seed);
+            const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)l16, 0u, seed);
             float z[4];
             bm_normal4_f32(bl, z);
 #pragma unroll
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(64 * kLowWPB) void row_lowrank(
     } else if constexpr (C == 2) {
         // components 2 l16, 2 l16 + 1: one Box-Muller pair of block l16 / 2
         if (2 * l16 < K) {
-            const Block4 bl = philox4x32_10(row, ctr[0], (stream << 24) | (uint32_t)(l16 >> 1), 0u, seed);
+            const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)(l16 >> 1), 0u, seed);
             const bool hi = (l16 & 1) != 0;
             float zc, zs;
             bm_pair_f32(hi ? bl.w2 : bl.w0, hi ? bl.w3 : bl.w1, zc, zs);
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(64 * kLowWPB) void row_lowrank(
         for (int e = 0; e < C; ++e) {
             const int c = C * l16 + e;
             if (c < K) {
-                const Block4 bl = philox4x32_10(row, ctr[0], (stream << 24) | (uint32_t)(c >> 2), 0u, seed);
+                const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)(c >> 2), 0u, seed);
                 const int m = c & 3;
                 vb[e] += bm_normal_f32(m < 2 ? bl.w0 : bl.w2, m < 2 ? bl.w1 : bl.w3, (m & 1) != 0);
             }
@@ -354,7 +354,7 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
                                (float)c->alpha, sd.items, beg, end, sd.nbr, (const float *)sd.rc,
                                (const float *)sd.Yt, c->ld, (const float *)sd.Linv_w,
                                (const float *)sd.Ltmu_w, (float *)sd.X, c->ld, c->seed, sd.stream_row,
-                               c->ctr);
+                               c->sweep_t());
         };
         using D4 = std::integral_constant<int, 4>;
         using D8 = std::integral_constant<int, 8>;
