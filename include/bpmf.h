@@ -235,8 +235,8 @@ int bpmf_last_time_ms(bpmf_ctx *c, double *ms);
  *     d* = W / (2P) - r, the smaller of the two sides';
  *   - for FP32 with 32 < K <= 64, whether rows take the column-per-lane
  *     (kmax 64) or the blocked (kmax 32) kernel;
- *   - for FP32 with K <= 64, the degree up to which rows take the rank-one
- *     update path (0 = off, 8, 16; a side uses it only where the saved
+ *   - for FP32, the degree up to which rows take the rank-one update path (0 =
+ *     off, 8, and 16 for K <= 64; a side uses it only where the saved
  *     factorisations outweigh transforming the gathered factor).
  * A candidate replaces the current plan only if it is at least 1% faster.
  * The chain state (factors, hyperparameters, running predictions, sweep

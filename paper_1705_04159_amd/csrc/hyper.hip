@@ -723,10 +723,10 @@ __global__ __launch_bounds__(NT) void hyper_draw(
     if (tid == 0 && !ok) *status = 0;
 }
 
-// For the rank-one row path (K <= 64) after (mu, Lambda) were set by the host:
+// For the rank-one row path after (mu, Lambda) were set by the host:
 // L^-1 and L^T mu = L^-1 (Lambda mu), L = chol(Lambda), FP64 in one workgroup.
-template <typename T>
-__global__ __launch_bounds__(256) void prior_factor(int K, const double *__restrict__ mu,
+template <int NT, typename T>
+__global__ __launch_bounds__(NT) void prior_factor(int K, const double *__restrict__ mu,
                                                     const double *__restrict__ Lam, T *__restrict__ Linv_w,
                                                     T *__restrict__ Ltmu_w, int *__restrict__ status)
 {
@@ -737,24 +737,25 @@ __global__ __launch_bounds__(256) void prior_factor(int K, const double *__restr
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15;
     if (tid == 0) ok = 1;
-    double w[10];
-    load_blocks<256, false>(nb, w, [&](int i, int j) {
+    constexpr int kFill = NT == 256 ? 10 : kMaxBlocks * (kMaxBlocks + 1) / 4;
+    double w[kFill];
+    load_blocks<NT, false>(nb, w, [&](int i, int j) {
         const int a = max(i, j), b = min(i, j);  // the lower triangle
         return a < K ? Lam[a * K + b] : (i == j ? 1.0 : 0.0);
     });
-    store_blocks<256, false>(nb, M1, w);
-    for (int i = tid; i < 16 * nb; i += 256) {
+    store_blocks<NT, false>(nb, M1, w);
+    for (int i = tid; i < 16 * nb; i += NT) {
         double s = 0.0;
         for (int j = 0; i < K && j < K; ++j) s += Lam[i >= j ? i * K + j : j * K + i] * mu[j];
         lm[i] = s;
     }
     __syncthreads();
-    chol_blocks<4>(nb, M1, &ok);
-    for (int b = wave; b < nb; b += 4) store_blk(M2 + bo(b, b), load_blk(M1 + bo(b, b), g, c), g, c);
+    chol_blocks<NT / 64>(nb, M1, &ok);
+    for (int b = wave; b < nb; b += NT / 64) store_blk(M2 + bo(b, b), load_blk(M1 + bo(b, b), g, c), g, c);
     __syncthreads();
-    inverse_blocks<4>(nb, M1, M2);
+    inverse_blocks<NT / 64>(nb, M1, M2);
     __syncthreads();
-    store_lower<4>(K, M2, Linv_w);
+    store_lower<NT / 64>(K, M2, Linv_w);
     tri_matvec<false>(K, nb, M2, lm, [&](int i, double x) { Ltmu_w[i] = (T)x; });
     if (tid == 0 && !ok) *status = 0;
 }
@@ -843,15 +844,25 @@ hipError_t prepare_hyper(bpmf_ctx *c)
 {
     const int need = (int)draw_lds(c->K);
     if (need <= 65536) return hipSuccess;  // only above K = 64 (FP32 factors, 512 threads)
-    return hipFuncSetAttribute((const void *)hyper_draw<512, float>, hipFuncAttributeMaxDynamicSharedMemorySize, need);
+    const hipError_t e =
+        hipFuncSetAttribute((const void *)hyper_draw<512, float>, hipFuncAttributeMaxDynamicSharedMemorySize, need);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute((const void *)prior_factor<512, float>, hipFuncAttributeMaxDynamicSharedMemorySize, need);
 }
 
 hipError_t launch_prior_to_working(bpmf_ctx *c, int side_id, hipStream_t s)
 {
     Side &sd = c->side[side_id];
     if (sd.n_low && c->prec == 1) {
-        hipLaunchKernelGGL((prior_factor<float>), dim3(1), dim3(256), draw_lds(c->K), s, c->K, sd.mu, sd.Lam,
-                           (float *)sd.Linv_w, (float *)sd.Ltmu_w, c->hyp_status);
+        auto factor = [&](auto ntc) {
+            constexpr int NT = decltype(ntc)::value;
+            hipLaunchKernelGGL((prior_factor<NT, float>), dim3(1), dim3(NT), draw_lds(c->K), s, c->K, sd.mu, sd.Lam,
+                               (float *)sd.Linv_w, (float *)sd.Ltmu_w, c->hyp_status);
+        };
+        if (c->K <= 64)
+            factor(std::integral_constant<int, 256>{});
+        else
+            factor(std::integral_constant<int, 512>{});
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

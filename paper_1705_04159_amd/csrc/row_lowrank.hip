@@ -1,5 +1,5 @@
 // row_lowrank.hip -- row update for rows with few ratings (d <= DMAX), FP32
-// factors, K <= 64: the Cholesky factor of P is built from chol(Lambda) by
+// factors, K <= 128: the Cholesky factor of P is built from chol(Lambda) by
 // rank-one updates instead of being factorised from scratch.
 //
 // The paper's shared-memory sampler uses a cheaper serial method for items
@@ -26,6 +26,8 @@
 // prefix and suffix sums run within the lane and then across the 16 lanes
 // by DPP row shifts.  Cost per row O(d^2 K + K^2 / 16) instructions instead
 // of the K^3 / 3 of a factorisation.
+#include <algorithm>
+
 #include "internal.h"
 #include "rng_device.h"
 #include "row_common.h"
@@ -125,191 +127,249 @@ __device__ __forceinline__ void solve_bwd(const Factor<C> &f, float (&v)[C])
 }
 
 // Yt[j] = L_Lam^-1 Y[j] for every row j of the gathered factor (padding 0).
+// A workgroup keeps L_Lam^-1 in LDS for its rounds of 256 / KP rows: one up to
+// K = 64, where more workgroups hide the rows' latency (5775 rows, K = 64: 13 us,
+// with eight rounds 22), eight above, where the matrix (64 KB at K = 128) is the
+// larger part.
+template <int KP>
+constexpr int transform_rounds()
+{
+    return KP <= 64 ? 1 : 8;
+}
+
 template <int KP>
 __global__ __launch_bounds__(256) void transform_rows(int K, const float *__restrict__ Y, int ld,
                                                       int64_t rows, const float *__restrict__ Linv,
                                                       float *__restrict__ Yt)
 {
+    constexpr int R = 256 / KP;  // rows at a time
     __shared__ float Ls[KP * KP];
     for (int q = threadIdx.x; q < KP * KP; q += 256) {
         const int r = q / KP, c = q % KP;
         Ls[q] = (r < K && c <= r) ? Linv[r * K + c] : 0.f;
     }
     __syncthreads();
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t j = g / KP;
-    const int c = (int)(g % KP);
-    if (j >= rows || c >= ld) return;
-    float s = 0.f;
-    if (c < K) {
-        const float *y = Y + (size_t)j * ld;
-        for (int m = 0; m <= c; ++m) s += Ls[c * KP + m] * y[m];
+    const int c = threadIdx.x % KP, sub = threadIdx.x / KP;
+    if (sub >= R || c >= ld) return;
+    for (int t = 0; t < transform_rounds<KP>(); ++t) {
+        const int64_t j = ((int64_t)blockIdx.x * transform_rounds<KP>() + t) * R + sub;
+        if (j >= rows) return;
+        double s = 0.0;  // every gathered row shares this rounding: FP64 sums
+        if (c < K) {
+            const float *y = Y + (size_t)j * ld;
+            for (int m = 0; m <= c; ++m) s += (double)Ls[c * KP + m] * (double)y[m];
+        }
+        Yt[(size_t)j * ld + c] = (float)s;
     }
-    Yt[(size_t)j * ld + c] = s;
 }
 
-constexpr int kLowWPB = 4;  // waves per workgroup; four rows per wave
+constexpr int kLowWPB = 4;       // waves per workgroup; four rows per wave
+constexpr int64_t kLowGroups = 4096;  // most workgroups of a launch
+
+// Workgroups take groups of 16 rows in turn.  The last product, x = L_Lam^-T v,
+// is the matrix product of the group's 16 vectors (through LDS) with
+// L_Lam^-1 on the matrix cores: wave w keeps the columns 16 w .. 16 w + 15 (and
+// 16 (w + 4) ..) of L_Lam^-1 as operands for all its groups, so that the matrix
+// needs no LDS (64 KB at K = 128).  Bound by the latency of a row's loads and
+// of the chain through its factors.  Above K = 64 the path replaces the blocked
+// factorisation for rows with at most 8 ratings: 245,784 rows, 1.5 M ratings,
+// K = 112: 3157 -> 950 us, 46,934 rows at K = 95: 487 -> 183; up to K = 64 the
+// launch takes as long as with the matrix in LDS (105 k rows, K = 64: 58 us).
+// Waves per SIMD that the registers of the factors (3 C DMAX) and of the
+// operands allow; left alone the compiler keeps more across the loop.
+template <int C, int DMAX>
+constexpr int low_waves()
+{
+    return C * DMAX <= 16 ? 4 : (C * DMAX <= 40 || C <= 4 ? 2 : 1);
+}
 
 template <int C, int DMAX>
-__global__ __launch_bounds__(64 * kLowWPB) void row_lowrank(
+__global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowrank(
     int K, float alpha, const RowItem *__restrict__ items, int64_t item0, int64_t n_items,
     const int32_t *__restrict__ nbr, const float *__restrict__ rc, const float *__restrict__ Yt,
     int ld, const float *__restrict__ Linv, const float *__restrict__ Ltmu, float *__restrict__ X,
     int ldx, uint64_t seed, uint32_t stream, SweepT sweep)
 {
     constexpr int KP = 16 * C;
-    __shared__ float Ms[KP * KP];  // Ms[m][c] = L_Lam^-1[m][c] (lower), padding 0
-    __shared__ float Vs[kLowWPB * 4 * KP];
-    for (int q = threadIdx.x; q < KP * KP; q += 64 * kLowWPB) {
-        const int m = q / KP, c = q % KP;
-        Ms[q] = (m < K && c <= m) ? Linv[m * K + c] : 0.f;
-    }
-    __syncthreads();
+    constexpr int VS = KP + 4;                          // row stride: 16 rows in different banks
+    constexpr int OWN = (C + kLowWPB - 1) / kLowWPB;  // 16-column blocks of a wave
+    __shared__ float Vs[4 * kLowWPB * VS];
+    __shared__ int row_s[4 * kLowWPB];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = lane >> 4, l16 = lane & 15;
-    const int64_t first = item0 + ((int64_t)blockIdx.x * kLowWPB + wave) * 4;
-    if (first >= n_items) return;
-    const int64_t id = first + grp;
-    const bool live = id < n_items;
-    RowItem it{-1, -1, 0, 0};
-    if (live) it = items[id];
-    const int d = (int)(it.end - it.beg);
-    // the wave's largest degree (items are in descending degree order)
-    const int dw = __builtin_amdgcn_readfirstlane((int)(items[first].end - items[first].beg));
     const float sa = __builtin_sqrtf(alpha);
-
-    float vb[C];
+    const uint32_t t_now = sweep.t();
+    // B operands: rows 16 mb + 4 s + grp of this wave's columns (lower: mb >= cb)
+    float bm[OWN][C][4];
 #pragma unroll
-    for (int e = 0; e < C; ++e) {
-        const int c = C * l16 + e;
-        vb[e] = c < K ? Ltmu[c] : 0.f;
-    }
-    Factor<C> F[DMAX];
-    // Up to 8 factors: every neighbour's id, rating and transformed row are
-    // loaded before the factors are built (two round trips to memory in
-    // all, not two per neighbour); the 16-factor instance has no registers
-    // to spare and loads them as it goes.
-    constexpr bool kPrefetch = DMAX <= 8;
-    float pa[kPrefetch ? DMAX : 1][C], pr[kPrefetch ? DMAX : 1];
-    if constexpr (kPrefetch) {
-        int pc[DMAX];
+    for (int o = 0; o < OWN; ++o)
 #pragma unroll
-        for (int j = 0; j < DMAX; ++j) {
-            pc[j] = j < d ? nbr[it.beg + j] : -1;
-            pr[j] = j < d ? rc[it.beg + j] : 0.f;
-        }
+        for (int mb = 0; mb < C; ++mb)
 #pragma unroll
-        for (int j = 0; j < DMAX; ++j)
-#pragma unroll
-            for (int e = 0; e < C; ++e) {
-                const int c = C * l16 + e;
-                pa[j][e] = (pc[j] >= 0 && c < K) ? sa * Yt[(size_t)pc[j] * ld + c] : 0.f;  // 0: identity factor
+            for (int s = 0; s < 4; ++s) {
+                const int m = 16 * mb + 4 * s + grp, c = 16 * (wave + kLowWPB * o) + l16;
+                bm[o][mb][s] = (m < K && c <= m) ? Linv[m * K + c] : 0.f;
             }
-    }
-    static_for<0, DMAX>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        if (j >= dw) return;  // uniform
-        float a[C];
-        float r = 0.f;
+    for (int64_t g0 = item0 + (int64_t)blockIdx.x * 4 * kLowWPB; g0 < n_items; g0 += (int64_t)gridDim.x * 4 * kLowWPB) {
+        const int64_t first = g0 + wave * 4;
+        const int64_t id = first + grp;
+        const bool live = id < n_items;
+        RowItem it{-1, -1, 0, 0};
+        if (live) it = items[id];
+        const int d = (int)(it.end - it.beg);
+        // the wave's largest degree (items are in descending degree order)
+        const int dw = __builtin_amdgcn_readfirstlane(d);
+
+        float vb[C];
+#pragma unroll
+        for (int e = 0; e < C; ++e) {
+            const int c = C * l16 + e;
+            vb[e] = c < K ? Ltmu[c] : 0.f;
+        }
+        Factor<C> F[DMAX];
+        // Up to 8 factors (4 above K = 64): every neighbour's id, rating and
+        // transformed row are loaded before the factors are built (two round
+        // trips to memory in all, not two per neighbour); the larger
+        // instances have no registers to spare and load them as they go.
+        constexpr bool kPrefetch = C * DMAX <= 32;
+        float pa[kPrefetch ? DMAX : 1][C], pr[kPrefetch ? DMAX : 1];
         if constexpr (kPrefetch) {
-            r = pr[j];
+            int pc[DMAX];
 #pragma unroll
-            for (int e = 0; e < C; ++e) a[e] = pa[j][e];
-        } else if (j < d) {
-            const int col = nbr[it.beg + j];
-            r = rc[it.beg + j];
+            for (int j = 0; j < DMAX; ++j) {
+                pc[j] = j < d ? nbr[it.beg + j] : -1;
+                pr[j] = j < d ? rc[it.beg + j] : 0.f;
+            }
 #pragma unroll
-            for (int e = 0; e < C; ++e) {
-                const int c = C * l16 + e;
-                a[e] = c < K ? sa * Yt[(size_t)col * ld + c] : 0.f;
+            for (int j = 0; j < DMAX; ++j)
+#pragma unroll
+                for (int e = 0; e < C; ++e) {
+                    const int c = C * l16 + e;
+                    pa[j][e] = (pc[j] >= 0 && c < K) ? sa * Yt[(size_t)pc[j] * ld + c] : 0.f;  // 0: identity factor
+                }
+        }
+        static_for<0, DMAX>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            if (j >= dw) return;  // uniform
+            float a[C];
+            float r = 0.f;
+            if constexpr (kPrefetch) {
+                r = pr[j];
+#pragma unroll
+                for (int e = 0; e < C; ++e) a[e] = pa[j][e];
+            } else if (j < d) {
+                const int col = nbr[it.beg + j];
+                r = rc[it.beg + j];
+#pragma unroll
+                for (int e = 0; e < C; ++e) {
+                    const int c = C * l16 + e;
+                    a[e] = c < K ? sa * Yt[(size_t)col * ld + c] : 0.f;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < C; ++e) a[e] = 0.f;  // identity factor
+            }
+            // b: alpha r' L^-1 y = sqrt(alpha) r' a
+#pragma unroll
+            for (int e = 0; e < C; ++e) vb[e] += sa * r * a[e];
+            static_for<0, j>([&](auto ic) { solve_fwd<C>(F[decltype(ic)::value], a); });
+            make_factor<C>(a, F[j]);
+        });
+        // y = L^-1 b, then + z
+        static_for<0, DMAX>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            if (i < dw) solve_fwd<C>(F[i], vb);
+        });
+        const uint32_t row = live ? (uint32_t)it.row : 0u;
+        if constexpr (C % 4 == 0) {
+            // components C l16 .. C l16 + C - 1: whole Philox blocks
+#pragma unroll
+            for (int b = 0; b < C / 4; ++b) {
+                const int blk = (C / 4) * l16 + b;
+                if (4 * blk < K) {
+                    const Block4 bl = philox4x32_10(row, t_now, (stream << 24) | (uint32_t)blk, 0u, seed);
+                    float z[4];
+                    bm_normal4_f32(bl, z);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (4 * blk + e < K) vb[4 * b + e] += z[e];
+                }
+            }
+        } else if constexpr (C % 2 == 0) {
+            // components C l16 ..: Box-Muller pairs 2 p, 2 p + 1 of block p / 2
+#pragma unroll
+            for (int b = 0; b < C / 2; ++b) {
+                const int p = (C / 2) * l16 + b;
+                if (2 * p < K) {
+                    const Block4 bl = philox4x32_10(row, t_now, (stream << 24) | (uint32_t)(p >> 1), 0u, seed);
+                    const bool hi = (p & 1) != 0;
+                    float zc, zs;
+                    bm_pair_f32(hi ? bl.w2 : bl.w0, hi ? bl.w3 : bl.w1, zc, zs);
+                    vb[2 * b] += zc;
+                    if (2 * p + 1 < K) vb[2 * b + 1] += zs;
+                }
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < C; ++e) a[e] = 0.f;  // identity factor
-        }
-        // b: alpha r' L^-1 y = sqrt(alpha) r' a
-#pragma unroll
-        for (int e = 0; e < C; ++e) vb[e] += sa * r * a[e];
-        static_for<0, j>([&](auto ic) { solve_fwd<C>(F[decltype(ic)::value], a); });
-        make_factor<C>(a, F[j]);
-    });
-    // y = L^-1 b, then + z
-    static_for<0, DMAX>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        if (i < dw) solve_fwd<C>(F[i], vb);
-    });
-    const uint32_t row = live ? (uint32_t)it.row : 0u;
-    if constexpr (C == 4) {
-        // components 4 l16 .. 4 l16 + 3: the four normals of Philox block l16
-        if (4 * l16 < K) {
-            const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)l16, 0u, seed);
-            float z[4];
-            bm_normal4_f32(bl, z);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (4 * l16 + e < K) vb[e] += z[e];
-        }
-    } else if constexpr (C == 2) {
-        // components 2 l16, 2 l16 + 1: one Box-Muller pair of block l16 / 2
-        if (2 * l16 < K) {
-            const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)(l16 >> 1), 0u, seed);
-            const bool hi = (l16 & 1) != 0;
-            float zc, zs;
-            bm_pair_f32(hi ? bl.w2 : bl.w0, hi ? bl.w3 : bl.w1, zc, zs);
-            vb[0] += zc;
-            if (2 * l16 + 1 < K) vb[1] += zs;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < C; ++e) {
-            const int c = C * l16 + e;
-            if (c < K) {
-                const Block4 bl = philox4x32_10(row, sweep.t(), (stream << 24) | (uint32_t)(c >> 2), 0u, seed);
-                const int m = c & 3;
-                vb[e] += bm_normal_f32(m < 2 ? bl.w0 : bl.w2, m < 2 ? bl.w1 : bl.w3, (m & 1) != 0);
+            for (int e = 0; e < C; ++e) {
+                const int c = C * l16 + e;
+                if (c < K) {
+                    const Block4 bl = philox4x32_10(row, t_now, (stream << 24) | (uint32_t)(c >> 2), 0u, seed);
+                    const int m = c & 3;
+                    vb[e] += bm_normal_f32(m < 2 ? bl.w0 : bl.w2, m < 2 ? bl.w1 : bl.w3, (m & 1) != 0);
+                }
             }
         }
-    }
-    // R_d^-T ... R_1^-T
-    static_for<0, DMAX>([&](auto qc) {
-        constexpr int i = DMAX - 1 - decltype(qc)::value;
-        if (i < dw) solve_bwd<C>(F[i], vb);
-    });
-    // x = L_Lam^-T v: x_c = sum_m Linv[m][c] v_m, with v through LDS and a
-    // rolled loop over m (an unrolled one keeps all K_pad x C matrix reads
-    // in flight at once)
-    float *vs = Vs + (wave * 4 + grp) * KP;
+        // R_d^-T ... R_1^-T
+        static_for<0, DMAX>([&](auto qc) {
+            constexpr int i = DMAX - 1 - decltype(qc)::value;
+            if (i < dw) solve_bwd<C>(F[i], vb);
+        });
 #pragma unroll
-    for (int e = 0; e < C; ++e) vs[C * l16 + e] = vb[e];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float x[C];
+        for (int e = 0; e < C; ++e) Vs[(wave * 4 + grp) * VS + C * l16 + e] = vb[e];
+        if (l16 == 0) row_s[wave * 4 + grp] = live ? it.row : -1;
+        __syncthreads();
+        // x_c = sum_m Linv[m][c] v_m for the 16 rows
 #pragma unroll
-    for (int e = 0; e < C; ++e) x[e] = 0.f;
-#pragma unroll 4
-    for (int m = 0; m < KP; ++m) {
-        const float vm = vs[m];
-        const float *mrow = Ms + m * KP + C * l16;
+        for (int o = 0; o < OWN; ++o) {
+            const int cb = wave + kLowWPB * o;
+            if (cb < C) {
+                floatx4 sum = {0.f, 0.f, 0.f, 0.f};  // of the blocks' own sums: shorter chains of roundings
 #pragma unroll
-        for (int e = 0; e < C; ++e) x[e] = fmaf(mrow[e], vm, x[e]);
-    }
-    if (live)
+                for (int mb = C - 1; mb >= 0; --mb)
+                    if (mb >= cb) {  // uniform
+                        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < C; ++e) {
-            const int c = C * l16 + e;
-            if (c < K) X[(size_t)it.row * ldx + c] = x[e];
+                        for (int s = 0; s < 4; ++s)
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Vs[l16 * VS + 16 * mb + 4 * s + grp],
+                                                                       bm[o][mb][s], acc, 0, 0, 0);
+                        sum += acc;
+                    }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int xr = row_s[4 * grp + v], c = 16 * cb + l16;
+                    if (xr >= 0 && c < K) X[(size_t)xr * ldx + c] = sum[v];
+                }
+            }
         }
+        __syncthreads();  // before the next group's vectors
+    }
 }
 
 }  // namespace
 
-// The low-rank path: FP32 factors, K <= 64, and the buffer-offset and row-id
-// limits of the matrix-core kernels (the same as the column-per-lane
-// kernel's), so that the factorisation kernels that run beside it stop at
-// the rank-one rows: the generic kernel would draw every row.
-bool lowrank_available(const bpmf_ctx *c) { return c->prec == 1 && c->K <= 64 && fast_path_available(c); }
+// The low-rank path: FP32 factors, K <= 128, and the buffer-offset and row-id
+// limits of the matrix-core kernels, so that the factorisation kernels that
+// run beside it stop at the rank-one rows: the generic kernel would draw
+// every row.
+bool lowrank_available(const bpmf_ctx *c)
+{
+    if (c->prec != 1 || c->K > 128) return false;
+    for (int s = 0; s < 2; ++s)
+        if ((uint64_t)c->side[s].rows * c->ld * sizeof(float) >= kOOB || c->side[s].rows >= (1 << 24)) return false;
+    return (uint64_t)c->split_threshold * 4u < kOOB;
+}
 
 // The rows stage of a side with low-rank rows: transform the gathered
 // factor, then the rows [n_items - n_low, n_items).  Degrees descend along
@@ -342,14 +402,14 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
     auto go = [&](auto cc) {
         constexpr int C = decltype(cc)::value;
         constexpr int KP = 16 * C;
-        const int64_t tot = ot.rows * (int64_t)KP;
-        hipLaunchKernelGGL((transform_rows<KP>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s,
+        const int64_t per = (256 / KP) * transform_rounds<KP>();
+        hipLaunchKernelGGL((transform_rows<KP>), dim3((unsigned)((ot.rows + per - 1) / per)), dim3(256), 0, s,
                            c->K, (const float *)ot.X, c->ld, ot.rows, (const float *)sd.Linv_w, sd.Yt);
         auto rows = [&](auto dc, int64_t beg, int64_t end) {
             constexpr int D = decltype(dc)::value;
             if (end <= beg) return;
-            const int64_t per_block = 4 * kLowWPB;
-            const unsigned grid = (unsigned)((end - beg + per_block - 1) / per_block);
+            const int64_t groups = (end - beg + 4 * kLowWPB - 1) / (4 * kLowWPB);
+            const unsigned grid = (unsigned)std::min<int64_t>(groups, kLowGroups);
             hipLaunchKernelGGL((row_lowrank<C, D>), dim3(grid), dim3(64 * kLowWPB), 0, s, c->K,
                                (float)c->alpha, sd.items, beg, end, sd.nbr, (const float *)sd.rc,
                                (const float *)sd.Yt, c->ld, (const float *)sd.Linv_w,
@@ -359,7 +419,10 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
         using D4 = std::integral_constant<int, 4>;
         using D8 = std::integral_constant<int, 8>;
         using D16 = std::integral_constant<int, 16>;
-        if (c->low_dmax > 8) {
+        if constexpr (C > 4) {  // the plan stops at 8 ratings above K = 64
+            rows(D8{}, item0, item_tiny);
+            rows(D4{}, item_tiny, sd.n_items);
+        } else if (c->low_dmax > 8) {
             rows(D16{}, item0, item_small);
             rows(D8{}, item_small, item_tiny);
             rows(D4{}, item_tiny, sd.n_items);
@@ -374,7 +437,11 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
     case 1: go(std::integral_constant<int, 1>{}); break;
     case 2: go(std::integral_constant<int, 2>{}); break;
     case 3: go(std::integral_constant<int, 3>{}); break;
-    default: go(std::integral_constant<int, 4>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 6: go(std::integral_constant<int, 6>{}); break;
+    case 7: go(std::integral_constant<int, 7>{}); break;
+    default: go(std::integral_constant<int, 8>{}); break;
     }
     return hipGetLastError();
 }

@@ -513,7 +513,7 @@ int bpmf_create(int64_t M, int64_t N, const int64_t *csr_ptr, const int32_t *csr
     // a segment's partial sums are large and its Gram long enough to keep
     // the waves busy)
     c->split_threshold = p->split_threshold > 0 ? p->split_threshold : (K > 64 ? 8192 : 2048);
-    // rank-one path for rows with at most 8 ratings where it pays (FP32, K <= 64)
+    // rank-one path for rows with at most 8 ratings where it pays (FP32)
     c->low_dmax = lowrank_available(c) ? 8 : 0;
     c->foldin_S = p->foldin_S > 0 ? p->foldin_S : 16;
     c->foldin_pool = p->foldin_pool_bytes;
@@ -990,7 +990,7 @@ int bpmf_autotune(bpmf_ctx *c, uint32_t n_sweeps, int32_t *chosen_split, int32_t
     std::vector<int> kmaxes = {c->fast_kmax};
     if (c->prec == BPMF_FP32 && c->K > 32 && c->K <= 64) kmaxes = {32, 64};
     std::vector<int> lows = {c->low_dmax};
-    if (lowrank_available(c)) lows = {0, 8, 16};
+    if (lowrank_available(c)) lows = c->K <= 64 ? std::vector<int>{0, 8, 16} : std::vector<int>{0, 8};
     const int old_split = c->split_threshold, old_kmax = c->fast_kmax, old_low = c->low_dmax;
     ChainSnapshot sn;
     if (int r = snapshot_take(c, sn)) {
@@ -1075,7 +1075,7 @@ int bpmf_set_plan(bpmf_ctx *c, int32_t split_threshold, int32_t fast_kmax, int32
     if (fast_kmax < 0 || fast_kmax > 64) return fail(c, BPMF_E_INVAL, "fast_kmax must be 0..64");
     if (lowrank_dmax != 0 && lowrank_dmax != 4 && lowrank_dmax != 8 && lowrank_dmax != 16)
         return fail(c, BPMF_E_INVAL, "lowrank_dmax must be 0, 4, 8 or 16");
-    if (lowrank_dmax && !lowrank_available(c))
+    if (lowrank_dmax && (c->K > 64 || !lowrank_available(c)))
         return fail(c, BPMF_E_INVAL, "the rank-one path needs FP32 factors and K <= 64");
     if (int rc = replan(c, split_threshold, fast_kmax, lowrank_dmax, true)) return rc;
     if (int rc = refresh_lowrank(c)) return rc;
