@@ -230,6 +230,9 @@ hipError_t launch_predict_pairs(bpmf_ctx *c, int64_t n, const int32_t *row, cons
 // device reads in place.
 hipError_t launch_predict_pairs_mapped(bpmf_ctx *c, int64_t n, const int32_t *row, const int32_t *col, float *out,
                                        hipStream_t s);
+// mu and Lambda of a side (K + K^2 values) into memory that the device writes in
+// place.
+hipError_t launch_read_hyper(bpmf_ctx *c, int side_id, double *out, hipStream_t s);
 // Caller ids to internal rows in place (relabelled contexts): row[e] and col[e]
 // through d_int_of of the user and movie sides.
 hipError_t launch_map_pairs(bpmf_ctx *c, int64_t n, int32_t *row, int32_t *col, hipStream_t s);

@@ -193,9 +193,12 @@ __global__ void predict_pairs(int K, int ld, int64_t n, const int32_t *__restric
 }
 
 // predict_pairs for ids and predictions in host memory and caller ids: a wave
-// moves 64 pairs' ids and results in whole 256-byte accesses (each crosses
-// PCIe once), maps the ids where the context is relabelled, and takes the
-// pairs four at a time, 16 lanes each, as predict_pairs does.
+// moves 16 pairs' ids and results in 64-byte accesses (each crosses PCIe
+// once), maps the ids where the context is relabelled, and takes the pairs
+// four at a time, 16 lanes each, as predict_pairs does.  Bound by the chain of
+// latencies id, map, row: 20,000 pairs 7.6 us (64 pairs a wave: 12.3).
+constexpr int kPairsPerWave = 16;
+
 template <typename T>
 __global__ __launch_bounds__(256) void predict_pairs_mapped(int K, int ld, int64_t n, const int32_t *__restrict__ row,
                                                             const int32_t *__restrict__ col,
@@ -205,24 +208,33 @@ __global__ __launch_bounds__(256) void predict_pairs_mapped(int K, int ld, int64
                                                             double rbar, float *__restrict__ out)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kPairsPerWave;
     if (base >= n) return;
     const int64_t e = base + lane;
-    int32_t r = e < n ? row[e] : 0, c = e < n ? col[e] : 0;
+    const bool mine_ok = lane < kPairsPerWave && e < n;
+    int32_t r = mine_ok ? row[e] : 0, c = mine_ok ? col[e] : 0;
     if (urow) {
         r = urow[r];
         c = vrow[c];
     }
     float mine = 0.f;
-#pragma unroll 4
-    for (int it = 0; it < 16; ++it) {
+#pragma unroll
+    for (int it = 0; it < kPairsPerWave / 4; ++it) {
         const int src = 4 * it + (lane >> 4);
         const int32_t rr = __shfl(r, src), cc = __shfl(c, src);  // pairs past n: row 0, not written
         const float p = (float)(group_dot<T>(K, U + (size_t)rr * ld, V + (size_t)cc * ld, lane & 15) + rbar);
         const float q = __shfl(p, (lane & 3) << 4);
         if (it == (lane >> 2)) mine = q;
     }
-    if (e < n) out[e] = mine;
+    if (mine_ok) out[e] = mine;
+}
+
+// mu, then Lambda, to host memory.
+__global__ __launch_bounds__(256) void read_hyper(int K, const double *__restrict__ mu, const double *__restrict__ Lam,
+                                                  double *__restrict__ out)
+{
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e < K + K * K) out[e] = e < K ? mu[e] : Lam[e - K];
 }
 
 __global__ void set_counter(uint32_t *ctr, int idx, uint32_t v) { ctr[idx] = v; }
@@ -334,11 +346,19 @@ hipError_t launch_predict_pairs(bpmf_ctx *c, int64_t n, const int32_t *row, cons
     return hipGetLastError();
 }
 
+hipError_t launch_read_hyper(bpmf_ctx *c, int side_id, double *out, hipStream_t s)
+{
+    const Side &sd = c->side[side_id];
+    hipLaunchKernelGGL(read_hyper, dim3((unsigned)((c->K + c->K * c->K + 255) / 256)), dim3(256), 0, s, c->K,
+                       (const double *)sd.mu, (const double *)sd.Lam, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_predict_pairs_mapped(bpmf_ctx *c, int64_t n, const int32_t *row, const int32_t *col, float *out,
                                        hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    const unsigned grid = (unsigned)((n + 255) / 256);
+    const unsigned grid = (unsigned)((n + 4 * kPairsPerWave - 1) / (4 * kPairsPerWave));
     auto go = [&](auto kern, auto *U, auto *V) {
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, c->K, c->ld, n, row, col,
                            (const int32_t *)c->d_int_of[0], (const int32_t *)c->d_int_of[1], U, V, c->rbar, out);

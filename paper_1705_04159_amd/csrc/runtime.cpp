@@ -1347,11 +1347,13 @@ int bpmf_get_hyper(bpmf_ctx *c, int32_t side, double *mu, double *Lambda)
 {
     STICKY(c);
     if (int r = check_side(c, side)) return r;
+    // one kernel writes both to the staging memory (two pageable copies: 45 us at K = 100)
+    const size_t K = (size_t)c->K;
+    const double *h = (const double *)c->io_pin;  // K + K^2 <= 128 + 128^2 values
+    HIPCK(c, launch_read_hyper(c, side, (double *)c->io_pin, c->stream));
     HIPCK(c, hipStreamSynchronize(c->stream));
-    if (mu) HIPCK(c, hipMemcpy(mu, c->side[side].mu, sizeof(double) * c->K, hipMemcpyDeviceToHost));
-    if (Lambda)
-        HIPCK(c, hipMemcpy(Lambda, c->side[side].Lam, sizeof(double) * c->K * c->K,
-                           hipMemcpyDeviceToHost));
+    if (mu) memcpy(mu, h, sizeof(double) * K);
+    if (Lambda) memcpy(Lambda, h + K, sizeof(double) * K * K);
     return BPMF_OK;
 }
 
