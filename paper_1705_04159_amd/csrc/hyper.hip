@@ -370,42 +370,6 @@ __device__ __forceinline__ void store_blk(double *X, doublex4 r, int g, int c)
     for (int v = 0; v < 4; ++v) X[(4 * v + g) * kBS + c] = r[v];
 }
 
-// x of lane k of each 16-lane row, and x of 16-lane row R, for every lane.
-template <int k>
-__device__ __forceinline__ double lane_of_row(double x)
-{
-    const uint64_t w = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, 0x150 + k, 0xf, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(w >> 32), 0x150 + k, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
-template <int R>
-__device__ __forceinline__ uint32_t row_of_wave(uint32_t x)
-{
-    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    const uint32_t y = (R & 1) ? p[1] : p[0];
-    const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-    return (R & 2) ? q[1] : q[0];
-}
-
-template <int R>
-__device__ __forceinline__ double row_of_wave(double x)
-{
-    const uint64_t w = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = row_of_wave<R>((uint32_t)w), hi = row_of_wave<R>((uint32_t)(w >> 32));
-    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
-// 1 / d to an ulp or so for normal d (estimate and two Newton steps: half the
-// dependent instructions of a division).
-__device__ __forceinline__ double rcp_f64(double d)
-{
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(fma(-d, r, 1.0), r, r);
-    return fma(fma(-d, r, 1.0), r, r);
-}
-
 // One wave: the whole symmetric block D = L L^T replaced by X = L^-1.  Lane
 // (g, c) holds rows 4 v + g of column c; column c > k takes -(d_kc / d_kk)
 // times column k on the stacked [G; d] (row k leaves d for G = L_unit^-T once

@@ -4,18 +4,23 @@
 //   P = Lambda + alpha sum_j y_j y_j^T,  b = Lambda mu + alpha sum_j r'_j y_j,
 //   P = L L^T,  y = L^-1 b,  x = L^-T (y + z).
 //
-// The layout of the FP32 kernel for K <= 64 in doubles.  Gram: v_mfma_f64_16x16x4_f64 on the lower 16 x 16
-// blocks of P, lane l holding component 16 bi + l % 16 of the neighbour row of
-// rating 4g + l / 16 (A operand of block row bi and B operand of block column
-// bj at once), gathered by buffer loads whose range check masks the ragged
-// tail.  Factorisation: the accumulators go through LDS into a
-// column-per-lane layout and are eliminated without square roots, b carried
-// as an extra row; pivot columns are broadcast by v_readlane (one row a wave)
-// or ds_swizzle (rows packed into lane groups).
+// Gram: v_mfma_f64_16x16x4_f64 on the 16 x 16 blocks of P's upper half, lane
+// l holding component 16 bi + l % 16 of the neighbour row of rating 4g + l / 16
+// (A operand of block row bi and B operand of block column bj at once),
+// gathered by buffer loads whose range check masks the ragged tail.  A
+// wavefront then factorises its row's blocks where they are, on the matrix
+// cores (row_f64_blocked); many light rows of K <= 16 go four to a wavefront
+// through LDS instead (row_f64_packed).
 //
-// What bounds it: at K = 32 the vector instructions of the factorisation
-// (about 530 FP64 FMAs and twice as many broadcasts a row) and, on problems
-// of a few thousand rows, the latency of one row's chain.
+// What bounds it: the FP64 vector instructions and the serial chain of the
+// 16 x 16 diagonal blocks; on problems of a few thousand rows the latency of
+// one row's chain.  Against a column-per-lane elimination (530 FP64 FMAs and
+// twice as many lane reads a row at K = 32), us a call, users / movies:
+//   6000 x 3500, 500 k ratings   K = 16  46.2 / 40.6 -> 34.9 / 36.6
+//                                K = 32  59.0 / 75.5 -> 50.4 / 55.2
+//                                K = 64   212 / 213  ->  137 / 139
+//   48,424 x 1252, 436 k         K = 21   178 / 57   ->  176 / 50
+//                                K = 49   972 / 153  ->  522 / 113
 #include <type_traits>
 
 #include "internal.h"
@@ -38,16 +43,6 @@ __device__ __forceinline__ double buf_f64_stream(__amdgpu_buffer_rsrc_t r, uint3
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, kStreamPolicy));
 }
 
-// 1 / d to an ulp or so for normal d: the hardware's estimate and two Newton
-// steps (half the dependent instructions of a division, which sits in the
-// chain of every elimination step).
-__device__ __forceinline__ double rcp_f64(double d)
-{
-    double r = __builtin_amdgcn_rcp(d);
-    r = fma(fma(-d, r, 1.0), r, r);
-    return fma(fma(-d, r, 1.0), r, r);
-}
-
 template <int RPW, int k>
 __device__ __forceinline__ double bcast_f64(double x)
 {
@@ -58,8 +53,28 @@ __device__ __forceinline__ double bcast_f64(double x)
     return __builtin_bit_cast(double, o);
 }
 
-// Gram (lower blocks; value v of lane l is D[4 v + l / 16][l % 16]) and rhs of
-// one work item.  Two chunks of 4 kU ratings: the rows of the next one and the
+__device__ __forceinline__ void wave_sync_f64()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Standard normal `comp` of a row: value comp % 4 of Philox block comp / 4, from
+// one Box-Muller pair.
+__device__ __forceinline__ double normal_f64(uint32_t row, uint32_t t, uint32_t comp, uint64_t seed,
+                                             uint32_t stream)
+{
+    const Block4 bl = philox4x32_10(row, t, (stream << 24) | (comp >> 2), 0u, seed);
+    const bool hi = (comp & 2) != 0;
+    const double rho = sqrt(-2.0 * log(open_unit(hi ? bl.w2 : bl.w0)));
+    double sv, cv;
+    sincospi(2.0 * open_unit(hi ? bl.w3 : bl.w1), &sv, &cv);
+    return rho * ((comp & 1) ? sv : cv);
+}
+
+// Gram (upper block (bj, bi), bi >= bj, in acc[bi (bi + 1) / 2 + bj]; value v of
+// lane l is D[4 v + l / 16][l % 16]) and rhs of one work item.  Two chunks of 4 kU ratings: the rows of the next one and the
 // ids of the one after are in flight while a chunk is multiplied.  Ratings
 // past the end and ids past the end read 0; components >= K read what follows
 // in the factor, whose Gram entries the caller ignores.
@@ -100,7 +115,7 @@ __device__ __forceinline__ void gram_item_f64(const RowItem &it, const int32_t *
             for (int bi = 0; bi < NB; ++bi) {
 #pragma unroll
                 for (int bj = 0; bj <= bi; ++bj, ++q)
-                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(yb[buf][g][bi], yb[buf][g][bj], acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(yb[buf][g][bj], yb[buf][g][bi], acc[q], 0, 0, 0);
                 bacc[bi] += rb[buf][g] * yb[buf][g][bi];
             }
         }
@@ -120,123 +135,96 @@ __device__ __forceinline__ void gram_item_f64(const RowItem &it, const int32_t *
     }
 }
 
-// Factor and sample one row held column-per-lane: lane c of the group has
-// v[r] = P[r][c] for r < KP (identity outside the leading K x K block) and
-// v[KP] = b_c.  Returns x_c (meaningful for c < K).  A live lane whose pivot
-// is not positive clears *status.
-template <int KP, int RPW>
-__device__ __forceinline__ double chol_sample_f64(double (&v)[KP + 1], int K, int c, uint32_t row, uint32_t t,
-                                                  uint64_t seed, uint32_t stream, bool live,
-                                                  int *__restrict__ status)
+constexpr int kWaves = 4;    // wavefronts per workgroup
+constexpr int kPackRows = 4;  // rows per wavefront of the packed kernel
+
+// Factor and sample four rows of K <= 16, column-per-lane in 16 lanes each:
+// lane c of a group has v[r] = P[r][c] for r < 16 (identity outside the
+// leading K x K block) and v[16] = b_c; elimination without square roots, b
+// carried as an extra row.  Returns x_c (meaningful for c < K).  A live lane
+// whose pivot is not positive clears *status.
+__device__ __forceinline__ double packed_sample_f64(double (&v)[17], int K, int c, uint32_t row, uint32_t t,
+                                                    uint64_t seed, uint32_t stream, bool live,
+                                                    int *__restrict__ status)
 {
     double mydiag = 1.0;
-    static_for<0, KP>([&](auto kc) {
+    static_for<0, 16>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         if (k >= K) return;  // uniform: the padding is the identity
-        const double dk = bcast_f64<RPW, k>(v[k]);
+        const double dk = bcast_f64<kPackRows, k>(v[k]);
         if (c == k) mydiag = dk;
         // lanes c <= k hold finished columns: multiplier 0 leaves them unchanged
         const double f = c > k ? v[k] * rcp_f64(dk) : 0.0;
-        static_for<k + 1, KP + 1>([&](auto rcc) {
+        static_for<k + 1, 17>([&](auto rcc) {
             constexpr int r = decltype(rcc)::value;
-            v[r] -= f * bcast_f64<RPW, k>(v[r]);
+            v[r] -= f * bcast_f64<kPackRows, k>(v[r]);
         });
     });
     if (live && !(mydiag > 0.0)) *status = 0;
     const double inv_s = rcp_f64(sqrt(mydiag));
 #pragma unroll
-    for (int r = 0; r < KP; ++r) v[r] *= inv_s;  // column c of L (rows > c)
+    for (int r = 0; r < 16; ++r) v[r] *= inv_s;  // column c of L (rows > c)
 
-    // w = L^-1 b + z: normal c is value c % 4 of block c / 4, from one
-    // Box-Muller pair
-    double w = v[KP] * inv_s;
-    if (c < K) {
-        const Block4 bl = philox4x32_10(row, t, (stream << 24) | (uint32_t)(c >> 2), 0u, seed);
-        const bool hi = (c & 2) != 0;
-        const double rho = sqrt(-2.0 * log(open_unit(hi ? bl.w2 : bl.w0)));
-        double sv, cv;
-        sincospi(2.0 * open_unit(hi ? bl.w3 : bl.w1), &sv, &cv);
-        w += rho * ((c & 1) ? sv : cv);
-    }
+    const double w = v[16] * inv_s + (c < K ? normal_f64(row, t, (uint32_t)c, seed, stream) : 0.0);
     // x = L^-T w, rows from the last (padded rows carry w = 0, x = 0)
     double accx = 0.0, myx = 0.0;
-    static_for<0, KP>([&](auto qc) {
-        constexpr int r = KP - 1 - decltype(qc)::value;
+    static_for<0, 16>([&](auto qc) {
+        constexpr int r = 15 - decltype(qc)::value;
         if (r >= K) return;  // uniform
-        const double xr = bcast_f64<RPW, r>((w - accx) * inv_s);
+        const double xr = bcast_f64<kPackRows, r>((w - accx) * inv_s);
         if (c == r) myx = xr;
         if (c < r) accx += v[r] * xr;
     });
     return myx;
 }
 
-// The Gram of a whole work item by one wavefront, raw, into a packed lower
-// triangle P with b behind it at `boff`.
-template <int NB>
+// The Gram of a whole work item of K <= 16 by one wavefront, raw, into a
+// packed lower triangle P with b behind it at `boff`.
 __device__ __forceinline__ void gram_to_lds(const RowItem &it, int K, const int32_t *__restrict__ nbr,
                                             const double *__restrict__ rc, __amdgpu_buffer_rsrc_t ysrc, int kq,
                                             int col, double *P, int boff)
 {
-    doublex4 acc[NB * (NB + 1) / 2];
-    double bacc[NB];
+    doublex4 acc[1] = {{0.0, 0.0, 0.0, 0.0}};
+    double bacc[1] = {0.0};
+    gram_item_f64<1>(it, nbr, rc, ysrc, (uint32_t)K * 8u, kq, col, acc, bacc);
+    bacc[0] += __shfl_xor(bacc[0], 16);
+    bacc[0] += __shfl_xor(bacc[0], 32);
 #pragma unroll
-    for (int q = 0; q < NB * (NB + 1) / 2; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int bi = 0; bi < NB; ++bi) bacc[bi] = 0.0;
-    gram_item_f64<NB>(it, nbr, rc, ysrc, (uint32_t)K * 8u, kq, col, acc, bacc);
-    int q = 0;
-#pragma unroll
-    for (int bi = 0; bi < NB; ++bi) {
-        bacc[bi] += __shfl_xor(bacc[bi], 16);
-        bacc[bi] += __shfl_xor(bacc[bi], 32);
-#pragma unroll
-        for (int bj = 0; bj <= bi; ++bj, ++q)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = 16 * bi + 4 * v + kq, c = 16 * bj + col;
-                if (r < K && c <= r) P[pk(r, c)] = acc[q][v];
-            }
-        const int c = 16 * bi + col;
-        if (kq == 0 && c < K) P[boff + c] = bacc[bi];
+    for (int v = 0; v < 4; ++v) {
+        const int r = 4 * v + kq;
+        if (r < K && col <= r) P[pk(r, col)] = acc[0][v];
     }
+    if (kq == 0 && col < K) P[boff + col] = bacc[0];
 }
 
-constexpr int kWaves = 4;  // wavefronts per workgroup
-
-// Workgroups [0, n_heavy) take one heavy item each, its ratings dealt to the
-// four wavefronts and their Grams summed in wave order; the others give each
-// wavefront RPW light rows.  With a wavefront to every item the launch lasted
-// as long as the longest rows: K = 32, 6000 x 3500 with 450 k ratings 171 us
-// (users, two a wave) and 99 us (movies).
-template <int NB, int RPW>
-__global__ __launch_bounds__(64 * kWaves) void row_f64(
+// K <= 16, many light rows.  Workgroups [0, n_heavy) take one heavy item each,
+// its ratings dealt to the four wavefronts and their Grams summed in wave
+// order; the others give each wavefront four light rows.
+__global__ __launch_bounds__(64 * kWaves) void row_f64_packed(
     int K, double alpha, const RowItem *__restrict__ items, int64_t n_heavy, int64_t n_items,
     const int32_t *__restrict__ nbr, const double *__restrict__ rc, const double *__restrict__ Y,
     uint32_t y_bytes, const double *__restrict__ Lam, const double *__restrict__ Lmu, double *__restrict__ X,
-    double *__restrict__ part, uint64_t seed, uint32_t stream, SweepT sweep,
-    int *__restrict__ status)
+    double *__restrict__ part, uint64_t seed, uint32_t stream, SweepT sweep, int *__restrict__ status)
 {
-    constexpr int KP = 16 * NB;
-    constexpr int LPR = 64 / RPW;
-    constexpr int PE = KP * (KP + 1) / 2;
-    constexpr int REGION = PE + KP;  // packed lower triangle, then b
-    __shared__ double Ps[kWaves * RPW * REGION];
+    constexpr int PE = 16 * 17 / 2;
+    constexpr int REGION = PE + 16;  // packed lower triangle, then b
+    __shared__ double Ps[kWaves * kPackRows * REGION];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, kq = lane >> 4;
     const __amdgpu_buffer_rsrc_t ysrc = make_rsrc(Y, y_bytes);
     const int KK2 = K * (K + 1) / 2;
-    double *Pw = Ps + wave * RPW * REGION;  // this wave's rows
-    int row_of[RPW];
+    double *Pw = Ps + wave * kPackRows * REGION;  // this wave's rows
+    int row_of[kPackRows];
 #pragma unroll
-    for (int h = 0; h < RPW; ++h) row_of[h] = -1;
+    for (int h = 0; h < kPackRows; ++h) row_of[h] = -1;
     if ((int64_t)blockIdx.x < n_heavy) {
         const RowItem it = items[blockIdx.x];
         const int64_t per = (it.end - it.beg + kWaves - 1) / kWaves;
         RowItem mine = it;
         mine.beg = min<int64_t>(it.end, it.beg + wave * per);
         mine.end = min<int64_t>(it.end, mine.beg + per);
-        gram_to_lds<NB>(mine, K, nbr, rc, ysrc, kq, col, Ps + wave * REGION, PE);
+        gram_to_lds(mine, K, nbr, rc, ysrc, kq, col, Ps + wave * REGION, PE);
         __syncthreads();
         double *dst = it.slot >= 0 ? part + (size_t)it.slot * (KK2 + K) : nullptr;
         for (int e = threadIdx.x; e < KK2 + K; e += 64 * kWaves) {
@@ -253,35 +241,255 @@ __global__ __launch_bounds__(64 * kWaves) void row_f64(
         if (dst || wave > 0) return;
         row_of[0] = it.row;
     } else {
-        const int64_t first = n_heavy + (((int64_t)blockIdx.x - n_heavy) * kWaves + wave) * RPW;
+        const int64_t first = n_heavy + (((int64_t)blockIdx.x - n_heavy) * kWaves + wave) * kPackRows;
         if (first >= n_items) return;
-        static_for<0, RPW>([&](auto hc) {
+        static_for<0, kPackRows>([&](auto hc) {
             constexpr int h = decltype(hc)::value;
             if (first + h >= n_items) return;
             const RowItem it = items[first + h];
-            gram_to_lds<NB>(it, K, nbr, rc, ysrc, kq, col, Pw + h * REGION, PE);
+            gram_to_lds(it, K, nbr, rc, ysrc, kq, col, Pw + h * REGION, PE);
             row_of[h] = it.row;
         });
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync_f64();
     }
 
-    const int grp = lane / LPR, c = lane & (LPR - 1);
+    const int grp = lane >> 4, c = lane & 15;
     int my_row = row_of[0];
 #pragma unroll
-    for (int h = 1; h < RPW; ++h)
+    for (int h = 1; h < kPackRows; ++h)
         if (grp == h) my_row = row_of[h];
     const bool live = my_row >= 0 && c < K;
     const double *P = Pw + grp * REGION;
-    const int cc = c < KP ? c : 0;
-    double v[KP + 1];
+    double v[17];
 #pragma unroll
-    for (int r = 0; r < KP; ++r)
-        v[r] = (live && r < K) ? Lam[r * K + c] + alpha * P[r >= cc ? pk(r, cc) : pk(cc, r)] : (r == c ? 1.0 : 0.0);
-    v[KP] = live ? Lmu[c] + alpha * P[PE + cc] : 0.0;
-    const double x = chol_sample_f64<KP, RPW>(v, K, c, (uint32_t)my_row, sweep.t(), seed, stream, live, status);
+    for (int r = 0; r < 16; ++r)
+        v[r] = (live && r < K) ? Lam[r * K + c] + alpha * P[r >= c ? pk(r, c) : pk(c, r)] : (r == c ? 1.0 : 0.0);
+    v[16] = live ? Lmu[c] + alpha * P[PE + c] : 0.0;
+    const double x = packed_sample_f64(v, K, c, (uint32_t)my_row, sweep.t(), seed, stream, live, status);
     if (live) X[(size_t)my_row * K + c] = x;
+}
+
+// Sum over the 16 lanes of each 16-lane row, left in lane 15 of the row.
+__device__ __forceinline__ double row_sum16_f64(double x)
+{
+    auto shr = [](double y, auto nc) {
+        constexpr int N = decltype(nc)::value;
+        const u32x2 w = __builtin_bit_cast(u32x2, y);
+        u32x2 o;
+        o.x = __builtin_amdgcn_update_dpp(0, (int)w.x, 0x110 + N, 0xf, 0xf, true);
+        o.y = __builtin_amdgcn_update_dpp(0, (int)w.y, 0x110 + N, 0xf, 0xf, true);
+        return __builtin_bit_cast(double, o);
+    };
+    x += shr(x, std::integral_constant<int, 1>{});
+    x += shr(x, std::integral_constant<int, 2>{});
+    x += shr(x, std::integral_constant<int, 4>{});
+    x += shr(x, std::integral_constant<int, 8>{});
+    return x;
+}
+
+// Blocked factorisation and draw of one row by one wave, the FP32 blocked
+// kernel's algorithm in doubles.  acc: the negated matrix -(Lambda + alpha G),
+// identity on the padding, as upper 16 x 16 blocks: block (i, j), i >= j, keeps
+// T[16 j + 4 v + g][16 i + c] in value v of lane (g, c), which is what every
+// product takes as operand and returns.  vec: b (n = 16 NB values), then room
+// for n more.  Only the diagonal blocks are eliminated on the vector units, all
+// 64 lanes busy; the rest are 16 x 16 products.
+template <int NB>
+__device__ __forceinline__ void blocked_sample_f64(doublex4 (&acc)[NB * (NB + 1) / 2], double *vec, int K,
+                                                   uint32_t row, uint32_t t, uint64_t seed, uint32_t stream,
+                                                   double *__restrict__ xrow, int *__restrict__ status)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    double *bv = vec, *xv = vec + 16 * NB;
+    double xa[NB][4];  // X_kb = L_kk^-1: X[c][4 v + g]
+    static_for<0, NB>([&](auto kbc) {
+        constexpr int kb = decltype(kbc)::value;
+        constexpr int qd = kb * (kb + 1) / 2 + kb;
+        // the diagonal block: column k' > k takes -(d_kk' / d_kk) times column k
+        // on [G; d], b's segment rides along
+        double u[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) u[v] = -acc[qd][v];
+        double bc = bv[16 * kb + c], mydiag = 1.0;
+        static_for<0, 16>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if (kb + 1 < NB || 16 * kb + k < K) {  // uniform: the padding is the identity
+                constexpr int gk = k & 3, vk = k >> 2;
+                const double pr = row_of_wave<gk>(u[vk]);
+                const double dk = lane_of_row<k>(pr);
+                if (c == k) mydiag = dk;
+                const double nf = c > k ? -pr * rcp_f64(dk) : 0.0;
+                if (g == gk) u[vk] = c == k ? 1.0 : 0.0;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) u[v] = fma(nf, lane_of_row<k>(u[v]), u[v]);
+                bc = fma(nf, lane_of_row<k>(bc), bc);
+            }
+        });
+        if (kb + 1 == NB)  // rows of the padding: G is the identity there
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (16 * kb + 4 * v + g >= K) u[v] = c == 4 * v + g ? 1.0 : 0.0;
+        if (g == 0 && 16 * kb + c < K && !(mydiag > 0.0)) *status = 0;
+        const double inv_s = rcp_f64(sqrt(mydiag));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) xa[kb][v] = u[v] * inv_s;
+        if (g == 0) bv[16 * kb + c] = bc * inv_s;  // y_kb
+        wave_sync_f64();
+        if constexpr (kb + 1 < NB) {
+            // R_kb,i = X T_kb,i, then b_i -= R_kb,i^T y_kb
+            double y[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y[v] = bv[16 * kb + 4 * v + g];
+            static_for<kb + 1, NB>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                constexpr int q = i * (i + 1) / 2 + kb;
+                doublex4 r = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    r = __builtin_amdgcn_mfma_f64_16x16x4f64(-xa[kb][v], acc[q][v], r, 0, 0, 0);
+                acc[q] = r;
+                double p = r[0] * y[0] + r[1] * y[1] + r[2] * y[2] + r[3] * y[3];
+                p += __shfl_xor(p, 16);
+                p += __shfl_xor(p, 32);
+                if (g == 0) bv[16 * i + c] -= p;
+            });
+            // T_j,i -= R_kb,j^T R_kb,i (the negated T takes the product)
+            static_for<kb + 1, NB>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                static_for<kb + 1, i + 1>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    constexpr int qi = i * (i + 1) / 2 + kb, qj = j * (j + 1) / 2 + kb, q = i * (i + 1) / 2 + j;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(acc[qj][v], acc[qi][v], acc[q], 0, 0, 0);
+                });
+            });
+            wave_sync_f64();
+        }
+    });
+    // w = y + z: lane l takes component l
+    if (lane < K) bv[lane] += normal_f64(row, t, (uint32_t)lane, seed, stream);
+    wave_sync_f64();
+    // x_kb = X^T (w_kb - sum_{i > kb} R_kb,i x_i), from the last block row
+    static_for<0, NB>([&](auto qc) {
+        constexpr int kb = NB - 1 - decltype(qc)::value;
+        if constexpr (kb + 1 < NB) {
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            static_for<kb + 1, NB>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                const double xc = xv[16 * i + c];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s[v] += acc[i * (i + 1) / 2 + kb][v] * xc;
+            });
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s[v] = row_sum16_f64(s[v]);
+                if (c == 15) bv[16 * kb + 4 * v + g] -= s[v];
+            }
+            wave_sync_f64();
+        }
+        const double wc = bv[16 * kb + c];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double o = row_sum16_f64(xa[kb][v] * wc);
+            if (c == 15) xv[16 * kb + 4 * v + g] = o;
+        }
+        wave_sync_f64();
+    });
+    if (lane < K) xrow[lane] = xv[lane];
+}
+
+// A light item for each wavefront; workgroups [0, n_heavy) take one heavy item
+// each, its ratings dealt to the four wavefronts and their Grams summed in wave
+// order.  Register budget: as many waves a SIMD as hold the blocks unspilled.
+template <int NB>
+__global__ __launch_bounds__(64 * kWaves, (NB <= 2 ? 4 : (NB == 3 ? 3 : 2))) void row_f64_blocked(
+    int K, double alpha, const RowItem *__restrict__ items, int64_t n_heavy, int64_t n_items,
+    const int32_t *__restrict__ nbr, const double *__restrict__ rc, const double *__restrict__ Y,
+    uint32_t y_bytes, const double *__restrict__ Lam, const double *__restrict__ Lmu, double *__restrict__ X,
+    double *__restrict__ part, uint64_t seed, uint32_t stream, SweepT sweep, int *__restrict__ status)
+{
+    constexpr int NBLK = NB * (NB + 1) / 2;
+    __shared__ double sums[NBLK * 256 + 64 * NB];
+    __shared__ double vecs[kWaves][32 * NB];
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool heavy = (int64_t)blockIdx.x < n_heavy;
+    const int64_t id = heavy ? (int64_t)blockIdx.x : n_heavy + ((int64_t)blockIdx.x - n_heavy) * kWaves + wave;
+    if (id >= n_items) return;
+    const RowItem it = items[id];
+    RowItem mine = it;
+    if (heavy) {
+        const int64_t per = (it.end - it.beg + kWaves - 1) / kWaves;
+        mine.beg = min<int64_t>(it.end, it.beg + wave * per);
+        mine.end = min<int64_t>(it.end, mine.beg + per);
+    }
+    doublex4 acc[NBLK];
+    double bacc[NB];
+#pragma unroll
+    for (int q = 0; q < NBLK; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int bi = 0; bi < NB; ++bi) bacc[bi] = 0.0;
+    gram_item_f64<NB>(mine, nbr, rc, make_rsrc(Y, y_bytes), (uint32_t)K * 8u, g, c, acc, bacc);
+    if (heavy) {
+        for (int w = kWaves - 1; w > 0; --w) {
+            if (wave == w) {
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sums[256 * q + 64 * v + lane] = acc[q][v];
+#pragma unroll
+                for (int bi = 0; bi < NB; ++bi) sums[256 * NBLK + 64 * bi + lane] = bacc[bi];
+            }
+            __syncthreads();
+            if (wave == w - 1) {
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[q][v] += sums[256 * q + 64 * v + lane];
+#pragma unroll
+                for (int bi = 0; bi < NB; ++bi) bacc[bi] += sums[256 * NBLK + 64 * bi + lane];
+            }
+        }
+        if (wave > 0) return;
+    }
+#pragma unroll
+    for (int bi = 0; bi < NB; ++bi) {
+        bacc[bi] += __shfl_xor(bacc[bi], 16);
+        bacc[bi] += __shfl_xor(bacc[bi], 32);
+    }
+    if (it.slot >= 0) {  // segment of a split row: raw partial sums, packed lower
+        const int KK2 = K * (K + 1) / 2;
+        double *dst = part + (size_t)it.slot * (KK2 + K);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+#pragma unroll
+            for (int j = 0; j <= i; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 16 * j + 4 * v + g, cc = 16 * i + c;
+                    if (cc < K && r <= cc) dst[pk(cc, r)] = acc[i * (i + 1) / 2 + j][v];
+                }
+            if (g == 0 && 16 * i + c < K) dst[KK2 + 16 * i + c] = bacc[i];
+        }
+        return;
+    }
+    double *vec = vecs[wave];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+#pragma unroll
+        for (int j = 0; j <= i; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * j + 4 * v + g, cc = 16 * i + c;
+                const int q = i * (i + 1) / 2 + j;
+                acc[q][v] = (r < K && cc < K) ? -alpha * acc[q][v] - Lam[r * K + cc] : (r == cc ? -1.0 : 0.0);
+            }
+        const int cc = 16 * i + c;
+        if (g == 0) vec[cc] = cc < K ? Lmu[cc] + alpha * bacc[i] : 0.0;
+    }
+    wave_sync_f64();
+    blocked_sample_f64<NB>(acc, vec, K, (uint32_t)it.row, sweep.t(), seed, stream, X + (size_t)it.row * K, status);
 }
 
 // Sum the partial slots of every split row into its first slot, in slot order
@@ -308,32 +516,49 @@ __global__ __launch_bounds__(256) void part_reduce_f64(const FinishItem *__restr
 
 // Split rows from their summed partials, one wavefront each.
 template <int NB>
-__global__ __launch_bounds__(64) void row_finish_f64(int K, double alpha, const FinishItem *__restrict__ fin,
-                                                     const double *__restrict__ part,
-                                                     const double *__restrict__ Lam,
-                                                     const double *__restrict__ Lmu, double *__restrict__ X,
-                                                     uint64_t seed, uint32_t stream,
-                                                     SweepT sweep, int *__restrict__ status)
+__global__ __launch_bounds__(64) void row_finish_f64(int K, double alpha,
+                                                             const FinishItem *__restrict__ fin,
+                                                             const double *__restrict__ part,
+                                                             const double *__restrict__ Lam,
+                                                             const double *__restrict__ Lmu,
+                                                             double *__restrict__ X, uint64_t seed,
+                                                             uint32_t stream, SweepT sweep,
+                                                             int *__restrict__ status)
 {
-    constexpr int KP = 16 * NB;
-    const int c = threadIdx.x;
+    __shared__ double vec[32 * NB];
+    const int g = threadIdx.x >> 4, c = threadIdx.x & 15;
     const FinishItem f = fin[blockIdx.x];
     const int KK2 = K * (K + 1) / 2;
-    const bool live = c < K;
     const double *src = part + (size_t)f.first * (KK2 + K);
-    double v[KP + 1];
+    doublex4 acc[NB * (NB + 1) / 2];
 #pragma unroll
-    for (int r = 0; r < KP; ++r)
-        v[r] = (live && r < K) ? Lam[r * K + c] + alpha * src[r >= c ? pk(r, c) : pk(c, r)] : (r == c ? 1.0 : 0.0);
-    v[KP] = live ? Lmu[c] + alpha * src[KK2 + c] : 0.0;
-    const double x = chol_sample_f64<KP, 1>(v, K, c, (uint32_t)f.row, sweep.t(), seed, stream, live, status);
-    if (live) X[(size_t)f.row * K + c] = x;
+    for (int i = 0; i < NB; ++i) {
+        const int cc = 16 * i + c;
+#pragma unroll
+        for (int j = 0; j <= i; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * j + 4 * v + g;
+                acc[i * (i + 1) / 2 + j][v] =
+                    (r < K && cc < K) ? -alpha * src[r >= cc ? pk(r, cc) : pk(cc, r)] - Lam[r * K + cc]
+                                      : (r == cc ? -1.0 : 0.0);
+            }
+        if (g == 0) vec[cc] = cc < K ? Lmu[cc] + alpha * src[KK2 + cc] : 0.0;
+    }
+    wave_sync_f64();
+    blocked_sample_f64<NB>(acc, vec, K, (uint32_t)f.row, sweep.t(), seed, stream, X + (size_t)f.row * K, status);
 }
 
-// Light rows up to which each takes a wavefront of its own: below it the GPU's
-// 1024 SIMDs have at most four waves each either way, and packing rows only
-// makes a wave walk their ratings one after the other.
-constexpr int64_t kUnpackedItems = 4096;
+// K <= 16: light rows above which four share a wavefront.  Packed, a wave walks
+// its rows' ratings one after the other but the chip needs a quarter of the
+// waves; 300 k ratings, us, a row a wave against packed, K = 10 / K = 16:
+//    8,000 users  27.8, 35.2 / 32.2, 36.1
+//   12,000        34.4, 35.9 / 40.8, 38.6
+//   16,000        41.2, 37.6 / 49.4, 40.3
+//   24,000        54.9, 38.4 / 67.1, 42.9
+// Above K = 16 a row a wave is at worst equal (48,424 rows: K = 21 176 against
+// 178 two a wave, K = 32 215 against 214) and up to 27% faster.
+constexpr int64_t kPackedAbove = 10240;
 
 template <int NB>
 hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
@@ -353,20 +578,18 @@ hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
     // the segments come first, then the whole rows in descending degree order
     const int64_t n_heavy = sd.n_slots + whole_rows_above(sd, heavy_limit(sd, c->nnz, K, 1024 * (NB <= 2 ? 3 : 2)));
     const int64_t n_light = sd.n_items - n_heavy;
-    auto go = [&](auto rpwc) {
-        constexpr int RPW = decltype(rpwc)::value;
-        const int64_t blocks = n_heavy + (n_light + RPW * kWaves - 1) / (RPW * kWaves);
-        hipLaunchKernelGGL((row_f64<NB, RPW>), dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, K, c->alpha,
-                           sd.items, n_heavy, sd.n_items, sd.nbr, (const double *)sd.rc, (const double *)ot.X,
+    auto go = [&](auto kernel, int rows_per_wave) {
+        const int64_t per = (int64_t)rows_per_wave * kWaves, blocks = n_heavy + (n_light + per - 1) / per;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * kWaves), 0, s, K, c->alpha, sd.items, n_heavy,
+                           sd.n_items, sd.nbr, (const double *)sd.rc, (const double *)ot.X,
                            (uint32_t)(ot.rows * K * sizeof(double)), (const double *)sd.Lam_w,
                            (const double *)sd.Lmu_w, (double *)sd.X, (double *)c->part, c->seed, sd.stream_row,
                            c->sweep_t(), c->hyp_status + 1);
     };
-    constexpr int kPacked = NB == 1 ? 4 : (NB == 2 ? 2 : 1);
-    if (n_light > kUnpackedItems)
-        go(std::integral_constant<int, kPacked>{});
+    if (NB == 1 && n_light > kPackedAbove)
+        go(row_f64_packed, kPackRows);
     else
-        go(std::integral_constant<int, 1>{});
+        go(row_f64_blocked<NB>, 1);
     return hipGetLastError();
 }
 
