@@ -1,8 +1,8 @@
 // row_generic.hip -- reference-shaped row update for any K <= 128 and every
 // precision: one workgroup of 256 threads per work item, Gram accumulated
 // from LDS tiles of gathered neighbour rows, Cholesky and both triangular
-// solves in LDS.  It is the FP64 path and the fallback for shapes the
-// matrix-core kernels do not cover.
+// solves in LDS.  It is the FP64 path above K = 64 and the fallback for shapes
+// the matrix-core kernels do not cover.
 //
 // Per row (Algorithm 1, the body of the movie and user loops; the
 // conditional is BPMF's):  P = Lambda + alpha sum_j y_j y_j^T,
