@@ -123,11 +123,13 @@ __global__ __launch_bounds__(64 * kScoreWaves) void foldin_score(
     }
 }
 
-// Order-preserving map of a float to an unsigned key (larger float, larger key).
+// Order-preserving map of a float to an unsigned key (larger float, larger key),
+// never 0, which marks the rated movies: the selection counts on a key for each
+// of the others, and the NaN of all ones would take 0.
 __device__ __forceinline__ uint32_t ord_key(float f)
 {
     const uint32_t u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    return max((u & 0x80000000u) ? ~u : (u | 0x80000000u), 1u);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave (lane order), and the

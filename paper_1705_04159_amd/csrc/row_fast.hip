@@ -514,7 +514,9 @@ __global__ __launch_bounds__(64 * WPB) void foldin_draw_f32(
     const float x = chol_sample_column<KP, RPW>(v, K, c, (uint32_t)key, (uint32_t)my_s,
                                                 (uint32_t)(key >> 32), seed, stream, live, status);
     const int64_t out_row = (int64_t)my_req * n_samples + my_s;
-    if (live) U[(size_t)out_row * ldu + c] = x;
+    // the padding too: the score multiplies all ldu components, and U's memory
+    // may hold anything (a NaN there makes every score of the request NaN)
+    if (my_req >= 0 && c < ldu) U[(size_t)out_row * ldu + c] = live ? x : 0.f;
 }
 
 // Sum the partial slots of every split row into its first slot, in slot
