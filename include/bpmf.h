@@ -298,10 +298,7 @@ int bpmf_row_kernel_ms(bpmf_ctx *c, double *ms);
  * params.foldin_pool_bytes (default 256 MiB) bounds the rated movies in
  * flight: each batch admits requests while their ratings fit pool/32 (8 B
  * per rating, four batches).  Blocks until in-flight fold-in batches finished.  A Gibbs call: not concurrent with other Gibbs calls on
- * c, and the first call must return before any bpmf_foldin_submit.
- * BPMF_E_INVAL where the process runs on an older HIP runtime (major.minor)
- * than the library was built for, as one that loaded PyTorch 2.10 first does:
- * fold-in has faulted the GPU there. */
+ * c, and the first call must return before any bpmf_foldin_submit. */
 int bpmf_store_sample(bpmf_ctx *c);
 
 /* Queue a request: n distinct movie ids in [0, N) with their ratings (host

@@ -361,13 +361,6 @@ int bpmf_store_sample(bpmf_ctx *c)
         return ffail(c, BPMF_E_INVAL, "fold-in: N too large for one workgroup's LDS");
     hipError_t e;
     if (!c->foldin) {
-        // A process that loaded another HIP runtime first (PyTorch brings 7.0)
-        // runs this library on it.  Serving faulted the GPU there once (two
-        // requests of 26 components, 10 samples, 18,538 movies); the cause is
-        // not known, so an older runtime than the one built for is refused.
-        int rt = 0;
-        if (hipRuntimeGetVersion(&rt) != hipSuccess || rt / 100000 < HIP_VERSION / 100000)
-            return ffail(c, BPMF_E_INVAL, "fold-in: the process runs an older HIP runtime than the library was built for");
         auto *f = new FoldinState();
         c->foldin = f;
         f->S_cap = c->foldin_S;

@@ -13,6 +13,22 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "slow: long-running CPU test")
 
 
+# Tests that hold a value which was wrong.  They stay as they are and run; each
+# is expected to fail, for the reason given.
+WRONG_VALUES = {
+    "test_gpu_foldin_runtime.py::test_refused_on_an_older_runtime":
+        "fold-in serves on older HIP runtimes again: the fault there was unwritten padding of the drawn factors "
+        "(test_gpu_foldin_padding.py, test_gpu_foldin_torch.py)",
+}
+
+
+def pytest_collection_modifyitems(items):
+    for item in items:
+        for name, why in WRONG_VALUES.items():
+            if item.nodeid.endswith(name):
+                item.add_marker(pytest.mark.xfail(strict=True, reason=why))
+
+
 @pytest.fixture(scope="session")
 def orc():
     import oracle
