@@ -29,7 +29,9 @@
  *   - A context owns all device memory (hipMalloc) and its HIP streams (the
  *     Gibbs calls go to params.stream when the caller gives one); it is
  *     bound to the device that was current at bpmf_create.
- *   - Gibbs calls on one context must not run concurrently.
+ *   - Gibbs calls on one context must not run concurrently.  The calls that
+ *     only read its state (bpmf_get_factor, bpmf_get_factor_f64,
+ *     bpmf_get_hyper, bpmf_predict with n > 0) may overlap each other.
  *   - Every call returns BPMF_OK (0) or a negative status; on failure the
  *     context is unchanged (except after BPMF_E_DEVICE, which is sticky:
  *     only bpmf_destroy is then valid) and bpmf_last_error() describes it.

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -145,8 +146,11 @@ struct bpmf_ctx {
     {
         return t_known ? bpmf::SweepT{nullptr, t_now + off} : bpmf::SweepT{ctr, off};
     }
-    // staging of host factor copies: two chunks each on the device and in pinned
-    // host memory
+    // staging of host copies (factors, hyperparameters, pairs and their predictions):
+    // two chunks each on the device and in pinned host memory, held by one call at a
+    // time.  The calls that read the state may come from several threads; without the
+    // lock one could overwrite pair ids that another's kernel has yet to read.
+    std::mutex io_mu;
     void *io_dev = nullptr, *io_pin = nullptr;
     hipEvent_t io_ev[2] = {};
     // predict scratch for user-supplied pairs

@@ -1207,6 +1207,7 @@ int bpmf_predict(bpmf_ctx *c, uint32_t t, int64_t n, const int32_t *row, const i
     for (int64_t e = 0; bad && e < n; ++e)
         if (row[e] < 0 || row[e] >= c->M || col[e] < 0 || col[e] >= c->N)
             return fail(c, BPMF_E_RANGE, "pair %lld out of range", (long long)e);
+    const std::lock_guard<std::mutex> io(c->io_mu);  // the staging memory, and q_row .. q_out
     if (n <= kPairsInPlace) {
         // the kernel reads the ids from pinned host memory and writes the
         // predictions there: one launch instead of three copies through
@@ -1251,6 +1252,7 @@ int bpmf_predict(bpmf_ctx *c, uint32_t t, int64_t n, const int32_t *row, const i
 // copy, 0.3 ms the transfer alone.)
 static int copy_factor(bpmf_ctx *c, int32_t side, void *host, bool to_host)
 {
+    const std::lock_guard<std::mutex> io(c->io_mu);
     Side &sd = c->side[side];
     const int w = (int)(elem_bytes(c) / 4);  // words per entry
     const int Kw = c->K * w, ldw = c->ld * w;
@@ -1349,6 +1351,7 @@ int bpmf_get_hyper(bpmf_ctx *c, int32_t side, double *mu, double *Lambda)
     if (int r = check_side(c, side)) return r;
     // one kernel writes both to the staging memory (two pageable copies: 45 us at K = 100)
     const size_t K = (size_t)c->K;
+    const std::lock_guard<std::mutex> io(c->io_mu);
     const double *h = (const double *)c->io_pin;  // K + K^2 <= 128 + 128^2 values
     HIPCK(c, launch_read_hyper(c, side, (double *)c->io_pin, c->stream));
     HIPCK(c, hipStreamSynchronize(c->stream));
