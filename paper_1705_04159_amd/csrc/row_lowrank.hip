@@ -164,23 +164,43 @@ __global__ __launch_bounds__(256) void transform_rows(int K, const float *__rest
 }
 
 constexpr int kLowWPB = 4;       // waves per workgroup; four rows per wave
-constexpr int64_t kLowGroups = 4096;  // most workgroups of a launch
+constexpr int64_t kLowGroups = 4096;  // most workgroups of a launch above K = 64
 
-// Workgroups take groups of 16 rows in turn.  The last product, x = L_Lam^-T v,
-// is the matrix product of the group's 16 vectors (through LDS) with
-// L_Lam^-1 on the matrix cores: wave w keeps the columns 16 w .. 16 w + 15 (and
-// 16 (w + 4) ..) of L_Lam^-1 as operands for all its groups, so that the matrix
-// needs no LDS (64 KB at K = 128).  Bound by the latency of a row's loads and
-// of the chain through its factors.  Above K = 64 the path replaces the blocked
-// factorisation for rows with at most 8 ratings: 245,784 rows, 1.5 M ratings,
-// K = 112: 3157 -> 950 us, 46,934 rows at K = 95: 487 -> 183; up to K = 64 the
-// launch takes as long as with the matrix in LDS (105 k rows, K = 64: 58 us).
+// Workgroups take groups of 16 rows.  The last product, x = L_Lam^-T v, is the
+// matrix product of the group's 16 vectors (through LDS) with L_Lam^-1 on the
+// matrix cores, wave w computing the columns 16 w .. 16 w + 15 (and 16 (w + 4) ..).
+// Up to K = 64 a workgroup takes one group and reads L_Lam^-1 from LDS (20 KB at
+// K = 64).  Above, where the matrix would be 64 KB, it takes groups in turn and
+// keeps its columns of L_Lam^-1 in registers.  Bound by the latency of a row's
+// loads and of the chain through its factors, so by the waves that the registers
+// leave room for: with the columns in registers up to K = 64 too, K = 64 took 190
+// registers (two waves a SIMD) for 8 ratings and spilled for 16; with the matrix
+// in LDS it takes 125 (four waves) and 220.  400,000 rows of 0 to 8 ratings, K =
+// 64: 341 us, 398 with the columns in registers, 367 with the last product on the
+// vector units; of 0 to 16 ratings, K = 32: 323, 415 and 339.  Above K = 64 the
+// path replaces the blocked factorisation for rows with at most 8 ratings:
+// 245,784 rows, 1.5 M ratings, K = 112: 3157 -> 950 us, 46,934 rows at K = 95:
+// 487 -> 183.
+template <int C>
+constexpr bool one_group()
+{
+    return C <= 4;
+}
+
+// Row stride of L_Lam^-1 in LDS: the four rows of an operand in different banks.
+template <int C>
+constexpr int linv_stride()
+{
+    return C % 2 ? 16 * C : 16 * C + 16;
+}
+
 // Waves per SIMD that the registers of the factors (3 C DMAX) and of the
 // operands allow; left alone the compiler keeps more across the loop.
 template <int C, int DMAX>
 constexpr int low_waves()
 {
-    return C * DMAX <= 16 ? 4 : (C * DMAX <= 40 || C <= 4 ? 2 : 1);
+    constexpr int n = C * DMAX;
+    return one_group<C>() ? (n <= 12 ? 8 : (n <= 16 ? 6 : (n <= 32 ? 4 : 2))) : (n <= 40 ? 2 : 1);
 }
 
 template <int C, int DMAX>
@@ -193,7 +213,9 @@ __global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowr
     constexpr int KP = 16 * C;
     constexpr int VS = KP + 4;                          // row stride: 16 rows in different banks
     constexpr int OWN = (C + kLowWPB - 1) / kLowWPB;  // 16-column blocks of a wave
+    constexpr int MS = linv_stride<C>();
     __shared__ float Vs[4 * kLowWPB * VS];
+    __shared__ float Ms[one_group<C>() ? KP * MS : 1];  // Ms[m][c] = L_Lam^-1[m][c] (lower), padding 0
     __shared__ int row_s[4 * kLowWPB];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -201,16 +223,30 @@ __global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowr
     const float sa = __builtin_sqrtf(alpha);
     const uint32_t t_now = sweep.t();
     // B operands: rows 16 mb + 4 s + grp of this wave's columns (lower: mb >= cb)
-    float bm[OWN][C][4];
+    float bm[one_group<C>() ? 1 : OWN][C][4];
+    if constexpr (one_group<C>()) {  // first read behind the barrier that the vectors need
+        float x[C * C];  // the loads of all entries in flight together
 #pragma unroll
-    for (int o = 0; o < OWN; ++o)
+        for (int u = 0; u < C * C; ++u) {
+            const int q = 64 * kLowWPB * u + threadIdx.x, m = q / KP, c = q % KP;
+            x[u] = Linv[min(m, K - 1) * K + min(c, K - 1)];
+        }
 #pragma unroll
-        for (int mb = 0; mb < C; ++mb)
+        for (int u = 0; u < C * C; ++u) {
+            const int q = 64 * kLowWPB * u + threadIdx.x, m = q / KP, c = q % KP;
+            Ms[m * MS + c] = (m < K && c <= m) ? x[u] : 0.f;
+        }
+    } else {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int m = 16 * mb + 4 * s + grp, c = 16 * (wave + kLowWPB * o) + l16;
-                bm[o][mb][s] = (m < K && c <= m) ? Linv[m * K + c] : 0.f;
-            }
+        for (int o = 0; o < OWN; ++o)
+#pragma unroll
+            for (int mb = 0; mb < C; ++mb)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int m = 16 * mb + 4 * s + grp, c = 16 * (wave + kLowWPB * o) + l16;
+                    bm[o][mb][s] = (m < K && c <= m) ? Linv[m * K + c] : 0.f;
+                }
+    }
     for (int64_t g0 = item0 + (int64_t)blockIdx.x * 4 * kLowWPB; g0 < n_items; g0 += (int64_t)gridDim.x * 4 * kLowWPB) {
         const int64_t first = g0 + wave * 4;
         const int64_t id = first + grp;
@@ -282,7 +318,29 @@ __global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowr
             if (i < dw) solve_fwd<C>(F[i], vb);
         });
         const uint32_t row = live ? (uint32_t)it.row : 0u;
-        if constexpr (C % 4 == 0) {
+        // (the cases up to K = 64 apart: in the loop forms the compiler keeps
+        // five to ten registers more through the factors)
+        if constexpr (C == 4) {
+            // components 4 l16 .. 4 l16 + 3: the four normals of Philox block l16
+            if (4 * l16 < K) {
+                const Block4 bl = philox4x32_10(row, t_now, (stream << 24) | (uint32_t)l16, 0u, seed);
+                float z[4];
+                bm_normal4_f32(bl, z);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * l16 + e < K) vb[e] += z[e];
+            }
+        } else if constexpr (C == 2) {
+            // components 2 l16, 2 l16 + 1: one Box-Muller pair of block l16 / 2
+            if (2 * l16 < K) {
+                const Block4 bl = philox4x32_10(row, t_now, (stream << 24) | (uint32_t)(l16 >> 1), 0u, seed);
+                const bool hi = (l16 & 1) != 0;
+                float zc, zs;
+                bm_pair_f32(hi ? bl.w2 : bl.w0, hi ? bl.w3 : bl.w1, zc, zs);
+                vb[0] += zc;
+                if (2 * l16 + 1 < K) vb[1] += zs;
+            }
+        } else if constexpr (C % 4 == 0) {
             // components C l16 .. C l16 + C - 1: whole Philox blocks
 #pragma unroll
             for (int b = 0; b < C / 4; ++b) {
@@ -341,9 +399,15 @@ __global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowr
                     if (mb >= cb) {  // uniform
                         floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
-                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Vs[l16 * VS + 16 * mb + 4 * s + grp],
-                                                                       bm[o][mb][s], acc, 0, 0, 0);
+                        for (int s = 0; s < 4; ++s) {
+                            float b;
+                            if constexpr (one_group<C>())
+                                b = Ms[(16 * mb + 4 * s + grp) * MS + 16 * cb + l16];
+                            else
+                                b = bm[o][mb][s];
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Vs[l16 * VS + 16 * mb + 4 * s + grp], b, acc,
+                                                                       0, 0, 0);
+                        }
                         sum += acc;
                     }
 #pragma unroll
@@ -353,6 +417,7 @@ __global__ __launch_bounds__(64 * kLowWPB, (low_waves<C, DMAX>())) void row_lowr
                 }
             }
         }
+        if constexpr (one_group<C>()) return;
         __syncthreads();  // before the next group's vectors
     }
 }
@@ -409,7 +474,7 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
             constexpr int D = decltype(dc)::value;
             if (end <= beg) return;
             const int64_t groups = (end - beg + 4 * kLowWPB - 1) / (4 * kLowWPB);
-            const unsigned grid = (unsigned)std::min<int64_t>(groups, kLowGroups);
+            const unsigned grid = (unsigned)(one_group<C>() ? groups : std::min<int64_t>(groups, kLowGroups));
             hipLaunchKernelGGL((row_lowrank<C, D>), dim3(grid), dim3(64 * kLowWPB), 0, s, c->K,
                                (float)c->alpha, sd.items, beg, end, sd.nbr, (const float *)sd.rc,
                                (const float *)sd.Yt, c->ld, (const float *)sd.Linv_w,
