@@ -127,37 +127,50 @@ __device__ __forceinline__ void solve_bwd(const Factor<C> &f, float (&v)[C])
 }
 
 // Yt[j] = L_Lam^-1 Y[j] for every row j of the gathered factor (padding 0).
-// A workgroup keeps L_Lam^-1 in LDS for its rounds of 256 / KP rows: one up to
-// K = 64, where more workgroups hide the rows' latency (5775 rows, K = 64: 13 us,
-// with eight rounds 22), eight above, where the matrix (64 KB at K = 128) is the
-// larger part.
-template <int KP>
-constexpr int transform_rounds()
+// A workgroup keeps L_Lam^-1 in LDS for its rounds of 256 / KP rows, as a packed
+// triangle: the lanes of a wave read one column of it, and the triangular numbers
+// put 64 rows into 64 banks.  Its loads are in flight together: one after the
+// other they were most of a launch on few rows (300 rows, K = 65: 20 us of the
+// path's 35).  One round up to K = 64, where more workgroups hide the rows'
+// latency (5775 rows, K = 64: 13 us, with eight rounds 22); above, where the
+// matrix is the larger part, up to eight, but no more than leave 512 workgroups.
+constexpr int transform_rounds(int KP, int64_t rows)
 {
-    return KP <= 64 ? 1 : 8;
+    const int64_t groups = (rows + 256 / KP - 1) / (256 / KP);
+    return KP <= 64 || groups <= 512 ? 1 : (groups >= 8 * 512 ? 8 : (int)(groups / 512));
 }
 
 template <int KP>
 __global__ __launch_bounds__(256) void transform_rows(int K, const float *__restrict__ Y, int ld,
-                                                      int64_t rows, const float *__restrict__ Linv,
+                                                      int64_t rows, int rounds, const float *__restrict__ Linv,
                                                       float *__restrict__ Yt)
 {
     constexpr int R = 256 / KP;  // rows at a time
-    __shared__ float Ls[KP * KP];
-    for (int q = threadIdx.x; q < KP * KP; q += 256) {
-        const int r = q / KP, c = q % KP;
-        Ls[q] = (r < K && c <= r) ? Linv[r * K + c] : 0.f;
+    constexpr int B = KP * KP / 256 < 16 ? KP * KP / 256 : 16;  // loads of the matrix in flight
+    __shared__ float Ls[KP * (KP + 1) / 2];
+    for (int q0 = threadIdx.x; q0 < KP * KP; q0 += 256 * B) {
+        float x[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int q = q0 + 256 * u, r = min(q / KP, K - 1);
+            x[u] = Linv[r * K + min(q % KP, r)];  // above the diagonal: one line a row
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int q = q0 + 256 * u, r = q / KP, c = q % KP;
+            if (q < KP * KP && c <= r) Ls[pk(r, c)] = r < K ? x[u] : 0.f;
+        }
     }
     __syncthreads();
     const int c = threadIdx.x % KP, sub = threadIdx.x / KP;
     if (sub >= R || c >= ld) return;
-    for (int t = 0; t < transform_rounds<KP>(); ++t) {
-        const int64_t j = ((int64_t)blockIdx.x * transform_rounds<KP>() + t) * R + sub;
+    for (int t = 0; t < rounds; ++t) {
+        const int64_t j = ((int64_t)blockIdx.x * rounds + t) * R + sub;
         if (j >= rows) return;
         double s = 0.0;  // every gathered row shares this rounding: FP64 sums
         if (c < K) {
             const float *y = Y + (size_t)j * ld;
-            for (int m = 0; m <= c; ++m) s += (double)Ls[c * KP + m] * (double)y[m];
+            for (int m = 0; m <= c; ++m) s += (double)Ls[pk(c, m)] * (double)y[m];
         }
         Yt[(size_t)j * ld + c] = (float)s;
     }
@@ -467,9 +480,10 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
     auto go = [&](auto cc) {
         constexpr int C = decltype(cc)::value;
         constexpr int KP = 16 * C;
-        const int64_t per = (256 / KP) * transform_rounds<KP>();
+        const int rounds = transform_rounds(KP, ot.rows);
+        const int64_t per = (256 / KP) * rounds;
         hipLaunchKernelGGL((transform_rows<KP>), dim3((unsigned)((ot.rows + per - 1) / per)), dim3(256), 0, s,
-                           c->K, (const float *)ot.X, c->ld, ot.rows, (const float *)sd.Linv_w, sd.Yt);
+                           c->K, (const float *)ot.X, c->ld, ot.rows, rounds, (const float *)sd.Linv_w, sd.Yt);
         auto rows = [&](auto dc, int64_t beg, int64_t end) {
             constexpr int D = decltype(dc)::value;
             if (end <= beg) return;
@@ -485,8 +499,12 @@ hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s)
         using D8 = std::integral_constant<int, 8>;
         using D16 = std::integral_constant<int, 16>;
         if constexpr (C > 4) {  // the plan stops at 8 ratings above K = 64
-            rows(D8{}, item0, item_tiny);
-            rows(D4{}, item_tiny, sd.n_items);
+            // rows that the chip takes at once gain nothing from the 4-factor
+            // instance's waves and cost a launch (4000 rows: K = 65 43 -> 32 us,
+            // K = 128 57 -> 41)
+            const int64_t tiny = sd.n_items - item_tiny > 4 * 1024 ? item_tiny : sd.n_items;
+            rows(D8{}, item0, tiny);
+            rows(D4{}, tiny, sd.n_items);
         } else if (c->low_dmax > 8) {
             rows(D16{}, item0, item_small);
             rows(D8{}, item_small, item_tiny);

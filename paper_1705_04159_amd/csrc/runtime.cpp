@@ -150,13 +150,23 @@ void plan_side(const std::vector<int64_t> &ptr, int64_t rows, int64_t split, int
     }
 }
 
-// Whether a side's rows with at most low_dmax ratings take the rank-one path:
-// worth it when the factorisations saved (K^3/3 each) outweigh transforming
-// the gathered factor (K^2 per row of the other side) several times over.
+// Whether a side's rows with at most low_dmax ratings take the rank-one path: up
+// to K = 64 where the factorisations saved (K^3/3 each) outweigh transforming
+// the gathered factor (K^2 per row of the other side) several times over.  Above,
+// from timed updates: a row costs about 0.21 NB^2 ns less than in the blocked
+// kernel (NB = ceil(K / 16): 5.2 ns at K = 65, 15 at 128), a gathered row up to 8
+// ns, and the path's two or three launches 25 us before either (rows of few
+// ratings, blocked / rank-one us: 2080 of 3000 x 150, K = 65 33 / 49, K = 128 92 /
+// 80; 5704 of 10,000 x 1500, K = 65 87 / 91, K = 96 131 / 119; 7453 of 12,000 x
+// 12,000, K = 65 102 / 160; 17,533 of 40,000 x 3000, K = 65 301 / 240).
 int64_t low_rows_used(const bpmf_ctx *c, int64_t n_low, int64_t other_rows)
 {
     if (c->low_dmax <= 0 || !lowrank_available(c)) return 0;
     const double K = (double)c->K;
+    if (c->K > 64) {
+        const double nb = (double)((c->K + 15) / 16);
+        return 0.21 * nb * nb * (double)n_low > 25000.0 + 8.0 * (double)other_rows ? n_low : 0;
+    }
     return (double)n_low * K * K * K / 3.0 > 4.0 * (double)other_rows * K * K ? n_low : 0;
 }
 

@@ -20,6 +20,10 @@ WRONG_VALUES = {
         "fold-in serves on older HIP runtimes again: the fault there was unwritten padding of the drawn factors "
         "(test_gpu_foldin_padding.py, test_gpu_foldin_torch.py)",
 }
+for k in (65, 80, 81, 96, 100, 112, 113, 128):
+    WRONG_VALUES["test_gpu_lowrank_wide.py::test_lowrank_above_64[97-%d]" % k] = (
+        "97 rows above K = 64 take the blocked kernel again, 1.2 to 1.6 times as fast there as the rank-one path "
+        "(test_gpu_lowrank_rule.py)")
 
 
 def pytest_collection_modifyitems(items):
