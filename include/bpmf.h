@@ -237,9 +237,11 @@ int bpmf_last_time_ms(bpmf_ctx *c, double *ms);
  *     d* = W / (2P) - r, the smaller of the two sides';
  *   - for FP32 with 32 < K <= 64, whether rows take the column-per-lane
  *     (kmax 64) or the blocked (kmax 32) kernel;
- *   - for FP32, the degree up to which rows take the rank-one update path (0 =
- *     off, 8, and 16 for K <= 64; a side uses it only where the saved
- *     factorisations outweigh transforming the gathered factor).
+ *   - for FP32 with K <= 64, the degree up to which rows take the rank-one
+ *     update path (0 = off, 8, 16; a side uses it only where the saved
+ *     factorisations outweigh transforming the gathered factor).  Above K = 64
+ *     rows with at most 8 ratings take it wherever that is faster by the
+ *     library's own rule, whatever the plan, and the value here is 0.
  * A candidate replaces the current plan only if it is at least 1% faster.
  * The chain state (factors, hyperparameters, running predictions, sweep
  * counter) is restored afterwards, so the chain continues as if no trial had
@@ -255,9 +257,10 @@ int bpmf_autotune(bpmf_ctx *c, uint32_t n_sweeps, int32_t *chosen_split, int32_t
  * (1..2^24; rows with more ratings are cut into segments of
  * max(128, split_threshold / 2)), fast_kmax (0..64; FP32 factors with
  * K <= fast_kmax take the column-per-lane kernel, larger K the blocked one)
- * and lowrank_dmax (0, 4, 8 or 16; with FP32 factors and K <= 64 every row
- * with at most that many ratings takes the rank-one update path -- unlike the
- * autotuner, without weighing the transform of the gathered factor).  The
+ * and lowrank_dmax (0 = off, 4, 8 or 16; with FP32 factors and K <= 64 every
+ * row with at most that many ratings takes the rank-one update path -- unlike
+ * the autotuner, without weighing the transform of the gathered factor; above
+ * K = 64 the library's rule stays in force and the value must be 0).  The
  * work items, finishing items and partial-sum workspace are rebuilt and the
  * sweep graph is re-captured (not launched) before returning; the chain
  * state is untouched and the samples do not depend on the plan beyond

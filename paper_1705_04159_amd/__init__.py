@@ -335,7 +335,8 @@ class Sampler:
 
     def set_plan(self, split_threshold, fast_kmax, lowrank_dmax):
         """Fix the split threshold, kernel family cut-off and rank-one cut-off
-        by hand (what autotune() would choose)."""
+        by hand (what autotune() would choose).  Above K = 64 the rank-one
+        cut-off must be 0: the library's own rule stays in force there."""
         self._check(lib().bpmf_set_plan(self._ctx, int(split_threshold), int(fast_kmax),
                                         int(lowrank_dmax)))
 

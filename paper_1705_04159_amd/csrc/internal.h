@@ -268,7 +268,7 @@ size_t row_generic_lds_bytes(int K, int prec);
 bool fast_path_available(const bpmf_ctx *c);
 // Row kernel for FP32 with 32 < K <= 128 and BF16-Gram with K <= 128.
 bool big_path_available(const bpmf_ctx *c);
-// Rank-one-update path for rows with few ratings (FP32, K <= 64).
+// Rank-one-update path for rows with few ratings (FP32, K <= 128).
 bool lowrank_available(const bpmf_ctx *c);
 hipError_t launch_row_lowrank(bpmf_ctx *c, int side_id, hipStream_t s);
 // Elements of one split-row partial slot: K(K+1)/2 + K packed for the

@@ -1000,7 +1000,10 @@ int bpmf_autotune(bpmf_ctx *c, uint32_t n_sweeps, int32_t *chosen_split, int32_t
     std::vector<int> kmaxes = {c->fast_kmax};
     if (c->prec == BPMF_FP32 && c->K > 32 && c->K <= 64) kmaxes = {32, 64};
     std::vector<int> lows = {c->low_dmax};
-    if (lowrank_available(c)) lows = c->K <= 64 ? std::vector<int>{0, 8, 16} : std::vector<int>{0, 8};
+    if (lowrank_available(c) && c->K <= 64) lows = {0, 8, 16};
+    // above K = 64 the cut-off is no part of the plan (low_rows_used decides):
+    // 0, which is what bpmf_set_plan takes there
+    auto reported = [c](int low) { return c->K <= 64 ? low : 0; };
     const int old_split = c->split_threshold, old_kmax = c->fast_kmax, old_low = c->low_dmax;
     ChainSnapshot sn;
     if (int r = snapshot_take(c, sn)) {
@@ -1022,7 +1025,7 @@ int bpmf_autotune(bpmf_ctx *c, uint32_t n_sweeps, int32_t *chosen_split, int32_t
             if (q < 64) {
                 if (tried_split) tried_split[q] = sp;
                 if (tried_kmax) tried_kmax[q] = km;
-                if (tried_low) tried_low[q] = ld;
+                if (tried_low) tried_low[q] = reported(ld);
                 if (tried_ms) tried_ms[q] = ms;
             }
             ++q;
@@ -1048,7 +1051,7 @@ int bpmf_autotune(bpmf_ctx *c, uint32_t n_sweeps, int32_t *chosen_split, int32_t
     if (rc != BPMF_OK) return rc;
     if (chosen_split) *chosen_split = best_split;
     if (chosen_kmax) *chosen_kmax = best_kmax;
-    if (chosen_low) *chosen_low = best_low;
+    if (chosen_low) *chosen_low = reported(best_low);
     if (n_tried) *n_tried = std::min(q, 64);
     return BPMF_OK;
 }
@@ -1086,8 +1089,9 @@ int bpmf_set_plan(bpmf_ctx *c, int32_t split_threshold, int32_t fast_kmax, int32
     if (lowrank_dmax != 0 && lowrank_dmax != 4 && lowrank_dmax != 8 && lowrank_dmax != 16)
         return fail(c, BPMF_E_INVAL, "lowrank_dmax must be 0, 4, 8 or 16");
     if (lowrank_dmax && (c->K > 64 || !lowrank_available(c)))
-        return fail(c, BPMF_E_INVAL, "the rank-one path needs FP32 factors and K <= 64");
-    if (int rc = replan(c, split_threshold, fast_kmax, lowrank_dmax, true)) return rc;
+        return fail(c, BPMF_E_INVAL, "lowrank_dmax needs FP32 factors and K <= 64 (above, the library's rule decides)");
+    const int low = c->K > 64 ? c->low_dmax : lowrank_dmax;
+    if (int rc = replan(c, split_threshold, fast_kmax, low, lowrank_dmax > 0)) return rc;
     if (int rc = refresh_lowrank(c)) return rc;
     return ensure_graph(c);  // so that the next timed sweeps do not include the capture
 }
