@@ -52,7 +52,7 @@ namespace bpmf {
 namespace {
 
 
-constexpr int kWaves = 4;      // waves per workgroup of row_big
+constexpr int kWaves = 4;      // waves per workgroup of row_big with heavy items
 constexpr int64_t kSimds = 1024;
 
 // Waves per SIMD the register allocation must allow (left alone, the
@@ -61,6 +61,17 @@ template <int NB>
 constexpr int big_waves()
 {
     return NB <= 3 ? 4 : (NB == 4 ? 3 : 2);
+}
+
+// Whether a chunk's rows are loaded together, and the next chunk's ids behind
+// them.  At NB = 8 those 72 registers do not fit beside 144 of accumulators
+// (segments of split rows spilled 24), so there a block of 16 components at a
+// time (FP32 K = 128, segments of 256 ratings, 17,770 movies: 1459 -> 1066 us
+// with the one-wave workgroups below).
+template <int NB>
+constexpr bool whole_chunks()
+{
+    return NB < 8;
 }
 
 // Per-wave LDS (floats): X = L_kk^-1 of every block row in the A-operand
@@ -126,7 +137,10 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
     // the first chunk starts the accumulators from zero (no separate clear)
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
+        constexpr bool WHOLE = whole_chunks<NB>();
         float r[8];
+        uint32_t base[8];
+        if constexpr (!WHOLE) load_ids(ch);
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
         // raw BF16 bits; pairs packed into dwords form the MFMA operand
         uint32_t yr[NB][8];
@@ -134,17 +148,21 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
         for (int e = 0; e < 8; ++e) {
             const uint32_t t = ch * 32 + 8 * kq + e;
             if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            uint32_t base = __umul24(jb[e], ldy2) + coff;  // fewer than 2^24 rows
-            if (last) base = t < cnt ? base : kOOB;
+            base[e] = __umul24(jb[e], ldy2) + coff;  // fewer than 2^24 rows
+            if (last) base[e] = t < cnt ? base[e] : kOOB;
+            if constexpr (WHOLE)
 #pragma unroll
-            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_u16(ysrc, base + 32u * bi) & 0xFFFFu;
+                for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_u16(ysrc, base[e] + 32u * bi) & 0xFFFFu;
         }
         u32x4 rp = u32x4{0u, 0u, 0u, 0u};
         if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, 0);
-        if (!last) load_ids(ch + 1);
+        if (WHOLE && !last) load_ids(ch + 1);
         bf16x8 y[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
+            if constexpr (!WHOLE)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) yr[bi][e] = buf_u16(ysrc, base[e] + 32u * bi) & 0xFFFFu;
             u32x4 w;
 #pragma unroll
             for (int h = 0; h < 4; ++h) w[h] = yr[bi][2 * h] | (yr[bi][2 * h + 1] << 16);
@@ -172,7 +190,7 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
         }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
-    load_ids(0);
+    if constexpr (whole_chunks<NB>()) load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -216,24 +234,31 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
     // of the chunk before have left, and the next chunk's ids behind them
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
-        float r[8], yr[NB][8];
+        constexpr bool WHOLE = whole_chunks<NB>();
+        float r[8], yr[WHOLE ? NB : 1][8];
+        uint32_t base[8];
+        if constexpr (!WHOLE) load_ids(ch);
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const uint32_t t = ch * 32 + 8 * kq + e;
             if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            uint32_t base = __umul24(jb[e], ldy4) + coff;  // fewer than 2^24 rows
-            if (last) base = t < cnt ? base : kOOB;
+            base[e] = __umul24(jb[e], ldy4) + coff;  // fewer than 2^24 rows
+            if (last) base[e] = t < cnt ? base[e] : kOOB;
+            if constexpr (WHOLE)
 #pragma unroll
-            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_f32(ysrc, base + 64u * bi);
+                for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_f32(ysrc, base[e] + 64u * bi);
         }
         u32x4 rp = u32x4{0u, 0u, 0u, 0u};
         if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, kStreamPolicy);
-        if (!last) load_ids(ch + 1);
+        if (WHOLE && !last) load_ids(ch + 1);
         bf16x8 H[NB], M[NB], L[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
-            const float (&yv)[8] = yr[bi];
+            if constexpr (!WHOLE)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) yr[0][e] = buf_f32(ysrc, base[e] + 64u * bi);
+            const float (&yv)[8] = yr[WHOLE ? bi : 0];
             if constexpr (!AUG) {
                 float s = 0.f;
 #pragma unroll
@@ -276,7 +301,7 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
             }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
-    load_ids(0);
+    if constexpr (whole_chunks<NB>()) load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -570,7 +595,7 @@ __global__ __launch_bounds__(64 * kWaves, big_waves<NB>()) void row_big(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const bool heavy = (int64_t)blockIdx.x < n_heavy;
     const int64_t id = item0 + (heavy ? (int64_t)blockIdx.x
-                                      : n_heavy + ((int64_t)blockIdx.x - n_heavy) * kWaves + wave);
+                                      : n_heavy + ((int64_t)blockIdx.x - n_heavy) * (blockDim.x >> 6) + wave);
     if (id >= n_items) return;
     const int col = lane & 15;
     const int kq = lane >> 4;
@@ -662,7 +687,7 @@ __global__ __launch_bounds__(64, big_waves<NB>()) void row_finish_big(
 {
     constexpr int NBLK = NB * (NB + 1) / 2;
     extern __shared__ float smem_f[];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     float *lds = smem_f;
     const FinishItem f = fin[blockIdx.x];
     // the row's partial slots summed in slot order (with `summed`, already
@@ -749,8 +774,14 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
     const bool aug = kr <= 13 && sd.rc3 != nullptr;
     auto go = [&](auto kern, int64_t item0, int64_t count, int64_t heavy) {
         if (count <= 0) return;
-        const unsigned grid = (unsigned)(heavy + (count - heavy + kWaves - 1) / kWaves);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), sizeof(float) * BigLds<NB>::GROUP, s, c->K,
+        // without heavy items one-wave workgroups, which give their LDS back row
+        // by row (60,000 rows of 25 ratings, FP32: K = 96 699 -> 683 us, K = 112 853
+        // -> 835)
+        const int waves = heavy ? kWaves : 1;
+        const bool seg = item0 < n_seg;  // segments need LDS for a heavy one's sum alone
+        const int lds = seg ? (heavy ? BigLds<NB>::SUM : 0) : (heavy ? BigLds<NB>::GROUP : BigLds<NB>::TOTAL);
+        const unsigned grid = (unsigned)(heavy + (count - heavy + waves - 1) / waves);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), sizeof(float) * lds, s, c->K,
                            (float)c->alpha, sd.items, item0, heavy, item0 + count, sd.nbr,
                            (const float *)sd.rc, (const uint16_t *)sd.rc3, (uint32_t)(c->nnz + 32), ysrc,
                            c->ld, y_bytes, img, (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
