@@ -575,8 +575,13 @@ hipError_t launch_f64(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
         return hipGetLastError();
     }
     if (stage != kStageSegments || sd.n_items == 0) return hipSuccess;
-    // the segments come first, then the whole rows in descending degree order
-    const int64_t n_heavy = sd.n_slots + whole_rows_above(sd, heavy_limit(sd, c->nnz, K, 1024 * (NB <= 2 ? 3 : 2)));
+    // the segments come first, then the whole rows in descending degree order.
+    // Waves a SIMD for the limit: the six that run at one block (movies of 60,000 x
+    // 17,770, K = 16: 170 us with three, 152 with six); above it one less than
+    // the four and three that run (movies of 12,000 x 500, K = 24: 45.5 us with three,
+    // 47.6 with four; K = 48 the same either way)
+    const int64_t n_heavy =
+        sd.n_slots + whole_rows_above(sd, heavy_limit(sd, c->nnz, K, 1024 * (NB == 1 ? 6 : (NB == 2 ? 3 : 2))));
     const int64_t n_light = sd.n_items - n_heavy;
     auto go = [&](auto kernel, int rows_per_wave) {
         const int64_t per = (int64_t)rows_per_wave * kWaves, blocks = n_heavy + (n_light + per - 1) / per;

@@ -953,7 +953,12 @@ static double model_split(const bpmf_ctx *c)
     const int K = c->K;
     const double r = 3.0 * K;
     double P;  // rows in flight: SIMDs x waves per SIMD x rows per wave of the kernel family
-    if (c->prec == BPMF_FP64) P = 512.0;  // one 256-thread workgroup per row
+    // FP64: not the 2048 to 24,576 rows that row_f64.hip holds in flight, since
+    // its rows above the heavy limit go to four waves and long ones lose less than a
+    // split row's partial sums cost; with 512 the fastest of 256, 512, ... 16,384 is
+    // tried (us a sweep at 512 / the fastest: 20,000 x 5000, K = 32 271 / 250 at 4096;
+    // 60,000 x 17,770, K = 10 423 / 379 at 8192; 12,000 x 500, K = 32 169 / 165 at 1024)
+    if (c->prec == BPMF_FP64) P = 512.0;
     else if (K <= 16) P = 1024.0 * 8 * 4;
     else if (K <= 32) P = 1024.0 * 7 * 2;
     else if (K <= 48) P = 1024.0 * 4;
