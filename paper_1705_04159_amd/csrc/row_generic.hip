@@ -1,13 +1,16 @@
 // row_generic.hip -- reference-shaped row update for any K <= 128 and every
 // precision: one workgroup of 256 threads per work item, Gram accumulated
 // from LDS tiles of gathered neighbour rows, Cholesky and both triangular
-// solves in LDS.  It is the FP64 path above K = 64 and the fallback for shapes
-// the matrix-core kernels do not cover.
+// solves in LDS.  It is the fallback for what the matrix-core kernels' 32-bit
+// buffer offsets and 24-bit row ids do not cover: a factor of 1 GiB or more, or a
+// side of 2^24 rows or more.
 //
 // Per row (Algorithm 1, the body of the movie and user loops; the
 // conditional is BPMF's):  P = Lambda + alpha sum_j y_j y_j^T,
 // b = Lambda mu + alpha sum_j r'_j y_j, P = L L^T, y = L^-1 b,
 // x = L^-T (y + z), z = Philox normals of counter (row, t, stream<<24|blk, 0).
+#include <algorithm>
+
 #include "internal.h"
 #include "rng_device.h"
 
@@ -238,15 +241,18 @@ hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage
     // this kernel draws every work item: a side must not also have rows on
     // the rank-one path (lowrank_available excludes every case that lands here)
     if (sd.n_low != 0) return hipErrorInvalidValue;
+    // a launch has fewer than 2^32 threads: at most 2^23 items each
+    auto update = [&](auto kern, size_t lds, auto alpha, auto *rc, auto *Y, auto *Lam, auto *Lmu, auto *X, auto *part) {
+        for (int64_t q = 0; q < sd.n_items; q += 1 << 23)
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>(sd.n_items - q, 1 << 23)), dim3(kThreads), lds, s,
+                               K, alpha, sd.items + q, sd.nbr, rc, Y, c->ld, Lam, Lmu, X, c->ld, part, c->seed,
+                               sd.stream_row, c->sweep_t(), c->hyp_status + 1);
+    };
     if (c->prec == 0) {
         size_t lds = lds_bytes<double>(K);
-        if (stage == kStageSegments && sd.n_items > 0)
-            hipLaunchKernelGGL((row_update_generic<double, double>), dim3((unsigned)sd.n_items),
-                               dim3(kThreads), lds, s, K, c->alpha, sd.items, sd.nbr,
-                               (const double *)sd.rc, (const double *)ot.X, c->ld,
-                               (const double *)sd.Lam_w, (const double *)sd.Lmu_w,
-                               (double *)sd.X, c->ld, (double *)c->part, c->seed, sd.stream_row,
-                               c->sweep_t(), c->hyp_status + 1);
+        if (stage == kStageSegments)
+            update(row_update_generic<double, double>, lds, c->alpha, (const double *)sd.rc, (const double *)ot.X,
+                   (const double *)sd.Lam_w, (const double *)sd.Lmu_w, (double *)sd.X, (double *)c->part);
         if (stage == kStageFinish && sd.n_fin > 0)
             hipLaunchKernelGGL((row_finish_generic<double>), dim3((unsigned)sd.n_fin),
                                dim3(kThreads), lds, s, K, c->alpha, sd.fin,
@@ -255,22 +261,15 @@ hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage
                                sd.stream_row, c->sweep_t(), c->hyp_status + 1);
     } else {
         size_t lds = lds_bytes<float>(K);
-        if (stage == kStageSegments && sd.n_items > 0) {
+        if (stage == kStageSegments) {
+            const float alpha = (float)c->alpha, *rc = (const float *)sd.rc, *Lam = (const float *)sd.Lam_w,
+                        *Lmu = (const float *)sd.Lmu_w;
             if (c->prec == 2)
-                hipLaunchKernelGGL((row_update_generic<float, uint16_t>),
-                                   dim3((unsigned)sd.n_items), dim3(kThreads), lds, s, K,
-                                   (float)c->alpha, sd.items, sd.nbr, (const float *)sd.rc,
-                                   (const uint16_t *)ot.Xbf, c->ld, (const float *)sd.Lam_w,
-                                   (const float *)sd.Lmu_w, (float *)sd.X, c->ld,
-                                   (float *)c->part, c->seed, sd.stream_row, c->sweep_t(),
-                                   c->hyp_status + 1);
+                update(row_update_generic<float, uint16_t>, lds, alpha, rc, (const uint16_t *)ot.Xbf, Lam, Lmu,
+                       (float *)sd.X, (float *)c->part);
             else
-                hipLaunchKernelGGL((row_update_generic<float, float>), dim3((unsigned)sd.n_items),
-                                   dim3(kThreads), lds, s, K, (float)c->alpha, sd.items, sd.nbr,
-                                   (const float *)sd.rc, (const float *)ot.X, c->ld,
-                                   (const float *)sd.Lam_w, (const float *)sd.Lmu_w,
-                                   (float *)sd.X, c->ld, (float *)c->part, c->seed,
-                                   sd.stream_row, c->sweep_t(), c->hyp_status + 1);
+                update(row_update_generic<float, float>, lds, alpha, rc, (const float *)ot.X, Lam, Lmu, (float *)sd.X,
+                       (float *)c->part);
         }
         if (stage == kStageFinish && sd.n_fin > 0)
             hipLaunchKernelGGL((row_finish_generic<float>), dim3((unsigned)sd.n_fin),
