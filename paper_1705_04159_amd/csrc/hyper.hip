@@ -787,15 +787,17 @@ hipError_t launch_hyper(bpmf_ctx *c, int side_id, hipStream_t s, uint32_t t_off)
     // the other side's row kernels; above, eight
     auto draw = [&](auto ntc) {
         constexpr int NT = decltype(ntc)::value;
-        if (c->prec == 0)
-            hipLaunchKernelGGL((hyper_draw<NT, double>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
-                               c->d_W0inv, c->beta0, sd.mu, sd.Lam, (double *)sd.Lam_w, (double *)sd.Lmu_w,
-                               (double *)nullptr, (double *)nullptr, c->hyp_status);
-        else
-            hipLaunchKernelGGL((hyper_draw<NT, float>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
-                               c->d_W0inv, c->beta0, sd.mu, sd.Lam, (float *)sd.Lam_w, (float *)sd.Lmu_w,
-                               sd.n_low ? (float *)sd.Linv_w : (float *)nullptr,
-                               sd.n_low ? (float *)sd.Ltmu_w : (float *)nullptr, c->hyp_status);
+        if constexpr (NT == 256)  // FP64 factors stop at K = 64
+            if (c->prec == 0) {
+                hipLaunchKernelGGL((hyper_draw<NT, double>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
+                                   c->d_W0inv, c->beta0, sd.mu, sd.Lam, (double *)sd.Lam_w, (double *)sd.Lmu_w,
+                                   (double *)nullptr, (double *)nullptr, c->hyp_status);
+                return;
+            }
+        hipLaunchKernelGGL((hyper_draw<NT, float>), dim3(1), dim3(NT), lds, s, K, rows, stats, noise, c->d_mu0,
+                           c->d_W0inv, c->beta0, sd.mu, sd.Lam, (float *)sd.Lam_w, (float *)sd.Lmu_w,
+                           sd.n_low ? (float *)sd.Linv_w : (float *)nullptr,
+                           sd.n_low ? (float *)sd.Ltmu_w : (float *)nullptr, c->hyp_status);
     };
     if (K <= 64)
         draw(std::integral_constant<int, 256>{});

@@ -220,8 +220,6 @@ inline int64_t whole_rows_above(const Side &sd, int64_t ratings)
 }
 
 // ---- launchers (defined in the .hip files; all enqueue on `s`) ----
-// Row update of one side: items, then split-row finishes.
-hipError_t launch_row_update(bpmf_ctx *c, int side_id, hipStream_t s);
 // Hyper draw of one side (statistics, reduction, single-workgroup draw) for
 // sweep ctr[0] + t_off.
 hipError_t launch_hyper(bpmf_ctx *c, int side_id, hipStream_t s, uint32_t t_off = 0);
@@ -262,8 +260,6 @@ hipError_t launch_split_ratings(bpmf_ctx *c, int side_id, hipStream_t s);
 // FP32 contexts whose matrix-core kernels take the rating planes rc3 for
 // the rhs of their three-part BF16 Gram.
 bool parts_gram_wanted(const bpmf_ctx *c);
-// Largest dynamic LDS a generic row kernel needs for K (bytes).
-size_t row_generic_lds_bytes(int K, int prec);
 // Fold-in kernels (FP32 factors, K <= 64).
 bool fast_path_available(const bpmf_ctx *c);
 // Row kernel for FP32 with 32 < K <= 128 and BF16-Gram with K <= 128.

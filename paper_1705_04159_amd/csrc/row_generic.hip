@@ -226,11 +226,6 @@ size_t lds_bytes(int K)
 
 }  // namespace
 
-size_t row_generic_lds_bytes(int K, int prec)
-{
-    return prec == 0 ? lds_bytes<double>(K) : lds_bytes<float>(K);
-}
-
 // One workgroup per work item; every item (segments and whole rows) in the
 // segments stage, the split rows in the finishing stage.
 hipError_t launch_row_generic(bpmf_ctx *c, int side_id, hipStream_t s, int stage)
