@@ -63,17 +63,6 @@ constexpr int big_waves()
     return NB <= 3 ? 4 : (NB == 4 ? 3 : 2);
 }
 
-// Whether a chunk's rows are loaded together, and the next chunk's ids behind
-// them.  At NB = 8 those 72 registers do not fit beside 144 of accumulators
-// (segments of split rows spilled 24), so there a block of 16 components at a
-// time (FP32 K = 128, segments of 256 ratings, 17,770 movies: 1459 -> 1066 us
-// with the one-wave workgroups below).
-template <int NB>
-constexpr bool whole_chunks()
-{
-    return NB < 8;
-}
-
 // Per-wave LDS (floats): X = L_kk^-1 of every block row in the A-operand
 // layout (one float4 per lane); the rhs b (becomes y), w and x.
 template <int NB>
@@ -137,10 +126,7 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
     // the first chunk starts the accumulators from zero (no separate clear)
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
-        constexpr bool WHOLE = whole_chunks<NB>();
         float r[8];
-        uint32_t base[8];
-        if constexpr (!WHOLE) load_ids(ch);
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
         // raw BF16 bits; pairs packed into dwords form the MFMA operand
         uint32_t yr[NB][8];
@@ -148,21 +134,17 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
         for (int e = 0; e < 8; ++e) {
             const uint32_t t = ch * 32 + 8 * kq + e;
             if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            base[e] = __umul24(jb[e], ldy2) + coff;  // fewer than 2^24 rows
-            if (last) base[e] = t < cnt ? base[e] : kOOB;
-            if constexpr (WHOLE)
+            uint32_t base = __umul24(jb[e], ldy2) + coff;  // fewer than 2^24 rows
+            if (last) base = t < cnt ? base : kOOB;
 #pragma unroll
-                for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_u16(ysrc, base[e] + 32u * bi) & 0xFFFFu;
+            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_u16(ysrc, base + 32u * bi) & 0xFFFFu;
         }
         u32x4 rp = u32x4{0u, 0u, 0u, 0u};
         if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, 0);
-        if (WHOLE && !last) load_ids(ch + 1);
+        if (!last) load_ids(ch + 1);
         bf16x8 y[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
-            if constexpr (!WHOLE)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) yr[bi][e] = buf_u16(ysrc, base[e] + 32u * bi) & 0xFFFFu;
             u32x4 w;
 #pragma unroll
             for (int h = 0; h < 4; ++h) w[h] = yr[bi][2 * h] | (yr[bi][2 * h + 1] << 16);
@@ -190,7 +172,7 @@ __device__ __forceinline__ void gram_item_bf16(const RowItem &it, const int32_t 
         }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
-    if constexpr (whole_chunks<NB>()) load_ids(0);
+    load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -231,34 +213,30 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
     uint32_t jb[8];
     auto load_ids = [&](uint32_t ch) { buf_ids8(jsrc, (ch * 32 + 8 * kq) * 4u, jb); };
     // a chunk's rows are loaded together, into the registers that the parts
-    // of the chunk before have left, and the next chunk's ids behind them
+    // of the chunk before have left, and the next chunk's ids behind them.  (At NB
+    // = 8 the 72 registers spill 12 to 24 beside 144 of accumulators, and still:
+    // K = 113, movies of 20,000 x 5000, 352 us against 558 with a block of 16
+    // components at a time, which spills none)
     auto chunk = [&](uint32_t ch, auto firstc) {
         constexpr bool FIRST = decltype(firstc)::value;
-        constexpr bool WHOLE = whole_chunks<NB>();
-        float r[8], yr[WHOLE ? NB : 1][8];
-        uint32_t base[8];
-        if constexpr (!WHOLE) load_ids(ch);
+        float r[8], yr[NB][8];
         const bool last = ch + 1 >= nchunk;  // only the last chunk (or chunk 0 of an empty item) runs past the end
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const uint32_t t = ch * 32 + 8 * kq + e;
             if constexpr (!AUG) r[e] = buf_f32_stream(rsrc, t * 4u);
-            base[e] = __umul24(jb[e], ldy4) + coff;  // fewer than 2^24 rows
-            if (last) base[e] = t < cnt ? base[e] : kOOB;
-            if constexpr (WHOLE)
+            uint32_t base = __umul24(jb[e], ldy4) + coff;  // fewer than 2^24 rows
+            if (last) base = t < cnt ? base : kOOB;
 #pragma unroll
-                for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_f32(ysrc, base[e] + 64u * bi);
+            for (int bi = 0; bi < NB; ++bi) yr[bi][e] = buf_f32(ysrc, base + 64u * bi);
         }
         u32x4 rp = u32x4{0u, 0u, 0u, 0u};
         if constexpr (AUG) rp = __builtin_amdgcn_raw_buffer_load_b128(psrc, poff + ch * 64u, 0, kStreamPolicy);
-        if (WHOLE && !last) load_ids(ch + 1);
+        if (!last) load_ids(ch + 1);
         bf16x8 H[NB], M[NB], L[NB];
 #pragma unroll
         for (int bi = 0; bi < NB; ++bi) {
-            if constexpr (!WHOLE)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) yr[0][e] = buf_f32(ysrc, base[e] + 64u * bi);
-            const float (&yv)[8] = yr[WHOLE ? bi : 0];
+            const float (&yv)[8] = yr[bi];
             if constexpr (!AUG) {
                 float s = 0.f;
 #pragma unroll
@@ -301,7 +279,7 @@ __device__ __forceinline__ void gram_item_p3t(const RowItem &it, const int32_t *
             }
     };
     // chunk 0 even for an empty item: every row it loads is 0 (out of range)
-    if constexpr (whole_chunks<NB>()) load_ids(0);
+    load_ids(0);
     chunk(0u, std::integral_constant<bool, true>{});
     for (uint32_t ch = 1; ch < nchunk; ++ch) chunk(ch, std::integral_constant<bool, false>{});
 }
@@ -776,7 +754,7 @@ hipError_t launch_big(bpmf_ctx *c, Side &sd, Side &ot, hipStream_t s, int stage)
         if (count <= 0) return;
         // without heavy items one-wave workgroups, which give their LDS back row
         // by row (60,000 rows of 25 ratings, FP32: K = 96 699 -> 683 us, K = 112 853
-        // -> 835)
+        // -> 835; segments of 256 ratings, K = 128, 17,770 movies: 1450 -> 1007)
         const int waves = heavy ? kWaves : 1;
         const bool seg = item0 < n_seg;  // segments need LDS for a heavy one's sum alone
         const int lds = seg ? (heavy ? BigLds<NB>::SUM : 0) : (heavy ? BigLds<NB>::GROUP : BigLds<NB>::TOTAL);
