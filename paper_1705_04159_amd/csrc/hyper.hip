@@ -710,8 +710,10 @@ __global__ __launch_bounds__(NT) void prior_factor(int K, const double *__restri
     store_blocks<NT, false>(nb, M1, w);
     for (int i = tid; i < 16 * nb; i += NT) {
         double s = 0.0;
-        for (int j = 0; i < K && j < K; ++j) s += Lam[i >= j ? i * K + j : j * K + i] * mu[j];
-        lm[i] = s;
+        const int ii = min(i, K - 1);
+#pragma unroll 16
+        for (int j = 0; j < K; ++j) s += Lam[ii >= j ? ii * K + j : j * K + ii] * mu[j];  // loads in flight together
+        lm[i] = i < K ? s : 0.0;
     }
     __syncthreads();
     chol_blocks<NT / 64>(nb, M1, &ok);
@@ -724,18 +726,23 @@ __global__ __launch_bounds__(NT) void prior_factor(int K, const double *__restri
     if (tid == 0 && !ok) *status = 0;
 }
 
-// Working-precision prior from FP64 (mu, Lambda) set by the host.
+// Working-precision prior from FP64 (mu, Lambda) set by the host: workgroup 0
+// Lambda mu, the others Lambda.
 template <typename T>
-__global__ void prior_to_working(int K, const double *__restrict__ mu, const double *__restrict__ Lam,
-                                 T *__restrict__ Lam_w, T *__restrict__ Lmu_w)
+__global__ __launch_bounds__(256) void prior_to_working(int K, const double *__restrict__ mu,
+                                                        const double *__restrict__ Lam, T *__restrict__ Lam_w,
+                                                        T *__restrict__ Lmu_w)
 {
-    int tid = threadIdx.x;
-    for (int i = tid; i < K; i += blockDim.x) {
+    const int tid = threadIdx.x;
+    if (blockIdx.x > 0) {
+        const int q = ((int)blockIdx.x - 1) * 256 + tid;
+        if (q < K * K) Lam_w[q] = (T)Lam[q];
+    } else if (tid < K) {
         double s = 0.0;
-        for (int j = 0; j < K; ++j) s += Lam[i * K + j] * mu[j];
-        Lmu_w[i] = (T)s;
+#pragma unroll 16
+        for (int j = 0; j < K; ++j) s += Lam[tid * K + j] * mu[j];  // loads in flight together
+        Lmu_w[tid] = (T)s;
     }
-    for (int q = tid; q < K * K; q += blockDim.x) Lam_w[q] = (T)Lam[q];
 }
 
 }  // namespace
@@ -832,11 +839,12 @@ hipError_t launch_prior_to_working(bpmf_ctx *c, int side_id, hipStream_t s)
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
+    const dim3 grid(1 + (unsigned)((c->K * c->K + 255) / 256));
     if (c->prec == 0)
-        hipLaunchKernelGGL((prior_to_working<double>), dim3(1), dim3(256), 0, s, c->K, sd.mu,
+        hipLaunchKernelGGL((prior_to_working<double>), grid, dim3(256), 0, s, c->K, sd.mu,
                            sd.Lam, (double *)sd.Lam_w, (double *)sd.Lmu_w);
     else
-        hipLaunchKernelGGL((prior_to_working<float>), dim3(1), dim3(256), 0, s, c->K, sd.mu,
+        hipLaunchKernelGGL((prior_to_working<float>), grid, dim3(256), 0, s, c->K, sd.mu,
                            sd.Lam, (float *)sd.Lam_w, (float *)sd.Lmu_w);
     return hipGetLastError();
 }
