@@ -129,11 +129,12 @@ __device__ __forceinline__ void solve_bwd(const Factor<C> &f, float (&v)[C])
 // Yt[j] = L_Lam^-1 Y[j] for every row j of the gathered factor (padding 0).
 // A workgroup keeps L_Lam^-1 in LDS for its rounds of 256 / KP rows, as a packed
 // triangle: the lanes of a wave read one column of it, and the triangular numbers
-// put 64 rows into 64 banks.  Its loads are in flight together: one after the
-// other they were most of a launch on few rows (300 rows, K = 65: 20 us of the
-// path's 35).  One round up to K = 64, where more workgroups hide the rows'
-// latency (5775 rows, K = 64: 13 us, with eight rounds 22); above, where the
-// matrix is the larger part, up to eight, but no more than leave 512 workgroups.
+// put 64 rows into 64 banks.  Its loads are in flight together; one after the
+// other they were most of a launch on few rows (97 rows that gather from 300, K =
+// 65: an update 55 us, 34 with this and the shared launch of the rank-one rows).
+// One round up to K = 64, where more workgroups hide the rows' latency (5775
+// rows, K = 64: 13 us, with eight rounds 22); above, where the matrix is the
+// larger part, up to eight, but no more than leave 512 workgroups.
 constexpr int transform_rounds(int KP, int64_t rows)
 {
     const int64_t groups = (rows + 256 / KP - 1) / (256 / KP);
